@@ -9,125 +9,18 @@
 //      (fp16 or bf16) and float32 accumulation, rounded to fp16 on chip, the
 //      convolution's halo recomputed per tile; H is stored in fp16, the
 //      operand type of the next product;
-//   2. gemm_nt_kernel: Y = H W_o^T (fp16 operands; bf16 weights are widened),
+//   2. gemm_ring_kernel: Y = H W_o^T (fp16 operands; bf16 weights are widened),
 //      float32 partial products per K slice summed by ksplit_reduce_kernel.
 // Weights use the layout of a linear layer (output features first), so both
 // operands of every product are read along K in 16-byte pieces.
 #include <hip/hip_runtime.h>
 
+#include "gemm.h"
 #include "gtr.h"
 #include "gtr_device.h"
 #include "gtr_internal.h"
 
 namespace gtr {
-
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned int w4 __attribute__((ext_vector_type(4)));
-
-// 8 consecutive K elements of one row as an MFMA operand. DT is the dtype of
-// the matrix in memory, MT the operand type (GTR_F16 or GTR_BF16).
-template <int DT, int MT>
-struct Operand;
-template <>
-struct Operand<GTR_F16, GTR_F16> {
-  typedef h8 T;
-  static __device__ __forceinline__ T get(w4 raw) { return __builtin_bit_cast(T, raw); }
-};
-template <>
-struct Operand<GTR_BF16, GTR_BF16> {
-  typedef bf8 T;
-  static __device__ __forceinline__ T get(w4 raw) { return __builtin_bit_cast(T, raw); }
-};
-template <>
-struct Operand<GTR_BF16, GTR_F16> {  // bf16 weights against fp16 activations
-  typedef h8 T;
-  static __device__ __forceinline__ T get(w4 raw) {
-    T r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const unsigned int u = raw[e];
-      r[2 * e] = (_Float16)__builtin_bit_cast(float, u << 16);
-      r[2 * e + 1] = (_Float16)__builtin_bit_cast(float, u & 0xffff0000u);
-    }
-    return r;
-  }
-};
-
-__device__ __forceinline__ f4 mfma(const h8& a, const h8& b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4 mfma(const bf8& a, const bf8& b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// C[M][N] = A[M][K] * B[N][K]^T, row-major, K a multiple of 64, N a multiple
-// of BN. Work-group tile BM x BN, 4 waves in a 2 x 2 grid, each wave a
-// (BM/2) x (BN/2) block of 16 x 16 MFMA tiles. Every K-step of 64 stages the
-// A and B tiles in LDS once (each element is read from memory by one thread
-// and from LDS by every wave that needs it) and runs two 32-deep MFMA passes
-// over them; the loads of the next steps are in flight while the current one
-// multiplies (two LDS buffers). Rows past M are read from row M-1 and not
-// stored. With ksplit > 1, K is cut into ksplit slices whose partial products
-// go to part + slice * M * N (float32) for ksplit_reduce_kernel; with
-// ksplit = 1 the product goes to C.
-// The grid is one-dimensional, gx * gy * ksplit work-groups (gx = ceil(M / BM),
-// gy = N / BN). Work-group b runs on XCD b % 8 (round-robin dispatch), and each
-// XCD takes a contiguous range of the tile order (slice, row block, column
-// block), column blocks fastest: the work-groups that read the same rows of A
-// (all column blocks of a row block and slice) share one XCD's L2 instead of
-// fetching those rows once per XCD.
-struct GemmArgs {
-  const void* A;
-  const void* B;
-  void* C;
-  float* part;
-  int M, N, K;
-  int cdt;     // dtype of C (GTR_F32 / GTR_F16 / GTR_BF16)
-  int ksplit;  // number of K slices (1: none)
-  const float* bias;  // [N] float32 added to every row, or null (ksplit = 1 only)
-  const void* res;    // [M][N] in C's dtype added elementwise (a residual), or null (ksplit = 1 only)
-  // head-major operands (ksplit = 1 only; 0: row-major):
-  int64_t a_tokens;   // A is [M / a_tokens][K / 64][a_tokens][64]: row m = (image m / a_tokens, token
-                      // m % a_tokens), K step s = head s (a head concat read in place)
-  int64_t c_tokens;   // C is written [N / (c_heads c_dim)][M / c_tokens][c_heads][c_tokens][c_dim]
-  int c_heads, c_dim;
-  float ln_eps;       // the row normalisation's epsilon (kernels with LN = 1)
-  int pad_;
-};
-
-// 8 consecutive 16-bit elements of dtype DT (one 16-byte piece) as floats.
-template <int DT>
-__device__ __forceinline__ void unpack_piece(const w4& v, float (&x)[8]) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const unsigned u = v[e];
-    if (DT == GTR_F16) {
-      x[2 * e] = (float)__builtin_bit_cast(_Float16, (unsigned short)(u & 0xffffu));
-      x[2 * e + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(u >> 16));
-    } else {
-      x[2 * e] = __builtin_bit_cast(float, u << 16);
-      x[2 * e + 1] = __builtin_bit_cast(float, u & 0xffff0000u);
-    }
-  }
-}
-
-// 4 consecutive elements of dtype dt at element offset off, as floats.
-__device__ __forceinline__ void load4(const void* base, int dt, int64_t off, float (&x)[4]) {
-  if (dt == GTR_F32) {
-    const f4 v = *reinterpret_cast<const f4*>(static_cast<const float*>(base) + off);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = v[e];
-  } else if (dt == GTR_F16) {
-    const h4 v = *reinterpret_cast<const h4*>(static_cast<const _Float16*>(base) + off);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = (float)v[e];
-  } else {
-    typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
-    const u16x4 v = *reinterpret_cast<const u16x4*>(static_cast<const unsigned short*>(base) + off);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = bf16_bits_to_f32(v[e]);
-  }
-}
 
 constexpr int KB = 4;     // minimum 64-wide K-steps per slice when splitting K
 // LDS tiles: rows of 32 K elements (64 bytes, no padding); the 16-byte piece
@@ -138,289 +31,6 @@ constexpr int KB = 4;     // minimum 64-wide K-steps per slice when splitting K
 // 4 pieces) both hit distinct slots.
 constexpr int kPitch = 32;
 __device__ __forceinline__ int kSwz(int r) { return (r >> 2) & 2; }
-// The output product's 64-wide rows (128 bytes, 8 pieces): piece c of row r at
-// c ^ kSwz64(r). Operand reads (16 rows x 2 pieces per 32 lanes) then hit 32
-// distinct slots (rows r, r + 4, r + 8, r + 12 share address / 16 mod 32 up to
-// the piece, and the swizzle gives them 4 disjoint piece pairs); staging writes
-// (2 rows x 8 pieces per 16 lanes) hit 16.
-constexpr int kPitch64 = 64;
-__device__ __forceinline__ int kSwz64(int r) { return ((r >> 2) & 3) << 1; }
-
-// With LN = 1 every row of A is normalised over its K columns (A' = (A - mu)
-// / sqrt(var + eps), a layer normalisation without affine weights, which the
-// caller folds into B and the bias) inside the product: the MFMAs multiply the
-// raw A, the row sums and squares of A and the row sums of B (colsum of B^T)
-// are taken from the pieces as they pass through registers on their way to
-// LDS, and the epilogue forms rs_m (C_mn - mu_m colsum_n), which is A' B^T in
-// real arithmetic. The squares are taken about a shift (the row's first
-// element) so that a row mean large next to its spread costs no precision.
-// LN = 1 needs K in one slice and a row-major A.
-template <int ADT, int BDT, int MT, int BM, int BN, int KW, int LN>
-__global__ void __launch_bounds__(256 * KW) gemm_nt_kernel(GemmArgs g) {
-  typedef Operand<ADT, MT> OA;
-  typedef Operand<BDT, MT> OB;
-  constexpr int NT = 256 * KW;                // threads
-  constexpr int TI = BM / 32, TJ = BN / 32;   // MFMA tiles per wave
-  constexpr int PA = BM * 8 / NT, PB = BN * 8 / NT;  // 16-byte pieces per thread per step
-  static_assert((KW == 1 || KW == 2) && PA >= 1 && PB >= 1 && BM * 8 % NT == 0 && BN * 8 % NT == 0,
-                "tiles split evenly over the threads");
-  static_assert(KW == 1 || BM * BN * 4 <= 2 * BM * kPitch64 * 2, "the K halves' partial sums fit in As");
-  __shared__ __attribute__((aligned(16))) unsigned short As[2][BM * kPitch64];
-  __shared__ __attribute__((aligned(16))) unsigned short Bs[2][BN * kPitch64];
-  __shared__ float lnst[LN ? 2 * BM : 1];  // per tile row: mean, 1 / sqrt(var + eps)
-  __shared__ float lncs[LN ? BN : 1];      // per tile column: the row sum of B
-
-  // wave w of the 2 x 2 grid over the tile; with KW = 2 the waves kh = 0 and
-  // kh = 1 take the first and the second 32-deep half of every K step
-  const int w = (threadIdx.x >> 6) & 3, kh = threadIdx.x >> 8, lane = threadIdx.x & 63;
-  const int r16 = lane & 15, kq = lane >> 4;
-  // tile of this work-group: XCD k = b % 8 takes positions [start_k, start_k +
-  // count_k) of the tile order, count_k = ceil((T - k) / 8)
-  const int gx = (g.M + BM - 1) / BM, gy = g.N / BN;
-  const int T = gx * gy * g.ksplit, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int j = xcd * (T >> 3) + min(xcd, T & 7) + slot;
-  const int by = j % gy, bxz = j / gy, bx = bxz % gx, bz = bxz / gx;
-  const int mb = bx * BM, nb = by * BN;
-  const int wm = (w >> 1) * (BM / 2), wn = (w & 1) * (BN / 2);
-  const unsigned short* A = static_cast<const unsigned short*>(g.A);
-  const unsigned short* B = static_cast<const unsigned short*>(g.B);
-  const int64_t K = g.K;
-  const int steps = g.K / 64;
-  const int s_per = (steps + g.ksplit - 1) / g.ksplit;
-  const int s0 = g.ksplit > 1 ? bz * s_per : 0;
-  const int s1 = min(s0 + s_per, steps);
-
-  // global pieces of this thread: piece p -> row p / 8, 16-byte column p % 8
-  const w4* ga[PA];
-  const w4* gb[PB];
-  int la[PA], lb[PB];
-#pragma unroll
-  for (int q = 0; q < PA; ++q) {
-    const int p = threadIdx.x + NT * q, row = p >> 3, col = p & 7;
-    const unsigned m = (unsigned)min(mb + row, g.M - 1), at = g.a_tokens ? (unsigned)g.a_tokens : 1u;
-    ga[q] = reinterpret_cast<const w4*>(
-        A + (g.a_tokens ? ((int64_t)(m / at) * (K / 64) * at + m % at) * 64 : (int64_t)m * K) + 8 * col);
-    la[q] = row * kPitch64 + 8 * (col ^ kSwz64(row));
-  }
-#pragma unroll
-  for (int q = 0; q < PB; ++q) {
-    const int p = threadIdx.x + NT * q, row = p >> 3, col = p & 7;
-    gb[q] = reinterpret_cast<const w4*>(B + (int64_t)(nb + row) * K + 8 * col);
-    lb[q] = row * kPitch64 + 8 * (col ^ kSwz64(row));
-  }
-  f4 acc[TI][TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-  // D K-steps of global loads in flight: a ring of register slots, each staged
-  // to LDS the step before it is multiplied (the loop is unrolled by D so
-  // every slot index is a compile-time constant)
-  constexpr int D = 4;
-  const int64_t ast = g.a_tokens ? 8 * g.a_tokens : 8;  // 16-byte pieces from one K step of A to the next
-  w4 ra[D][PA], rb[D][PB];
-  auto fetch = [&](int st, w4 (&a)[PA], w4 (&b)[PB]) {
-#pragma unroll
-    for (int q = 0; q < PA; ++q) a[q] = ga[q][ast * st];
-#pragma unroll
-    for (int q = 0; q < PB; ++q) b[q] = gb[q][8 * st];
-  };
-  auto stage = [&](int buf, const w4 (&a)[PA], const w4 (&b)[PB]) {
-#pragma unroll
-    for (int q = 0; q < PA; ++q) *reinterpret_cast<w4*>(&As[buf][la[q]]) = a[q];
-#pragma unroll
-    for (int q = 0; q < PB; ++q) *reinterpret_cast<w4*>(&Bs[buf][lb[q]]) = b[q];
-  };
-  // row statistics (LN = 1) of the steps staged so far: per piece of A the
-  // sum and the sum of squares about the row's shift, per piece of B its sum
-  float sh[PA], sa[PA], sq[PA], cb[PB];
-#pragma unroll
-  for (int q = 0; q < PA; ++q) sh[q] = sa[q] = sq[q] = 0.f;
-#pragma unroll
-  for (int q = 0; q < PB; ++q) cb[q] = 0.f;
-  auto stats = [&](const w4 (&a)[PA], const w4 (&b)[PB]) {
-    if constexpr (LN != 0) {
-#pragma unroll
-      for (int q = 0; q < PA; ++q) {
-        float x[8];
-        unpack_piece<ADT>(a[q], x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float d = x[e] - sh[q];
-          sa[q] += d;
-          sq[q] = fmaf(d, d, sq[q]);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < PB; ++q) {
-        float x[8];
-        unpack_piece<BDT>(b[q], x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cb[q] += x[e];
-      }
-    }
-  };
-  auto mma = [&](int buf) {
-#pragma unroll
-    for (int hh = 0; hh < 2 / KW; ++hh) {  // the 32-deep halves of the step this wave takes
-      const int h = KW == 1 ? hh : kh;
-      const int pc = (4 * h + kq) ^ kSwz64(r16);
-      typename OA::T fa[TI];
-      typename OB::T fb[TJ];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-        fa[i] = OA::get(*reinterpret_cast<const w4*>(&As[buf][(wm + 16 * i + r16) * kPitch64 + 8 * pc]));
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        fb[j] = OB::get(*reinterpret_cast<const w4*>(&Bs[buf][(wn + 16 * j + r16) * kPitch64 + 8 * pc]));
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = mfma(fb[j], fa[i], acc[i][j]);  // C^T tiles
-    }
-  };
-  // The loop runs whole groups of D steps in which every step issues the same
-  // loads (past the slice's last step they re-read that step, never used):
-  // with no load under a branch the compiler's waits count exactly, so a step
-  // waits for the loads of the step it stages, not for the newer ones (which
-  // matters where few work-groups run, each a chain of K steps). The last
-  // (steps mod D) steps follow with their loads already in flight.
-  if (s1 > s0) {
-#pragma unroll
-    for (int q = 0; q < D; ++q) fetch(min(s0 + q, s1 - 1), ra[q], rb[q]);
-    if constexpr (LN != 0) {  // the shift of each row: its first element, from the row's column-0 lane
-#pragma unroll
-      for (int q = 0; q < PA; ++q) {
-        float x[8];
-        unpack_piece<ADT>(ra[0][q], x);
-        sh[q] = __shfl(x[0], lane & ~7, kWave);
-      }
-    }
-    stage(0, ra[0], rb[0]);
-    stats(ra[0], rb[0]);
-    __syncthreads();
-    int sb = s0;
-    for (; sb + D <= s1; sb += D) {
-#pragma unroll
-      for (int q = 0; q < D; ++q) {
-        const int st = sb + q, buf = (st - s0) & 1;
-        fetch(min(st + D, s1 - 1), ra[q], rb[q]);  // slot q was staged before this step
-        mma(buf);
-        stage(buf ^ 1, ra[(q + 1) % D], rb[(q + 1) % D]);  // nobody reads buf ^ 1 now
-        if (st + 1 < s1) stats(ra[(q + 1) % D], rb[(q + 1) % D]);  // past the last step: a re-read
-        __syncthreads();
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < D - 1; ++q) {
-      const int st = sb + q, buf = (st - s0) & 1;
-      if (st < s1) {
-        mma(buf);
-        if (st + 1 < s1) {
-          stage(buf ^ 1, ra[(q + 1) % D], rb[(q + 1) % D]);
-          stats(ra[(q + 1) % D], rb[(q + 1) % D]);
-        }
-        __syncthreads();
-      }
-    }
-  }
-
-  if constexpr (LN != 0) {  // the 8 lanes of a row combine; lane 0 of each stores
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-#pragma unroll
-      for (int q = 0; q < PA; ++q) {
-        sa[q] += __shfl_xor(sa[q], o, kWave);
-        sq[q] += __shfl_xor(sq[q], o, kWave);
-      }
-#pragma unroll
-      for (int q = 0; q < PB; ++q) cb[q] += __shfl_xor(cb[q], o, kWave);
-    }
-    if ((lane & 7) == 0) {
-      const float inv = 1.f / (float)g.K;
-#pragma unroll
-      for (int q = 0; q < PA; ++q) {
-        const int row = (threadIdx.x + NT * q) >> 3;
-        const float m1 = sa[q] * inv;
-        lnst[2 * row] = sh[q] + m1;
-        lnst[2 * row + 1] = rsqrtf(fmaxf(sq[q] * inv - m1 * m1, 0.f) + g.ln_eps);
-      }
-#pragma unroll
-      for (int q = 0; q < PB; ++q) lncs[(threadIdx.x + NT * q) >> 3] = cb[q];
-    }
-    if (KW == 1) __syncthreads();
-  }
-  if (KW == 2) {  // the second K half's sums join the first's through LDS
-    f4* red = reinterpret_cast<f4*>(&As[0][0]);
-    __syncthreads();  // every wave is past the K loop's last LDS read
-    if (kh == 1) {
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) red[((w * TI + i) * TJ + j) * 64 + lane] = acc[i][j];
-    }
-    __syncthreads();
-    if (kh == 1) return;
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] += red[((w * TI + i) * TJ + j) * 64 + lane];
-  }
-
-  // lane holds C[row 16i + r16][columns 16j + 4kq .. 16j + 4kq + 3] of this
-  // wave's block (the products above are C^T tiles): one 4-element store each
-  void* C = g.ksplit > 1 ? static_cast<void*>(g.part + (int64_t)bz * g.M * g.N) : g.C;
-  const int cdt = g.ksplit > 1 ? (int)GTR_F32 : g.cdt;
-  // head-major C: element (m, n) at (((p img + b) heads + h) tokens + t) dim + c
-  // with m = b tokens + t, n = (p heads + h) dim + c; the divisions are 32-bit
-  // (the host keeps M below 2^31) and taken once per row and column block
-  const bool hmc = g.ksplit == 1 && g.c_tokens != 0;
-  const unsigned tokens = hmc ? (unsigned)g.c_tokens : 1u, cdim = hmc ? (unsigned)g.c_dim : 1u;
-  const unsigned hd = hmc ? (unsigned)(g.c_heads * g.c_dim) : 1u, img = (unsigned)g.M / tokens;
-  int64_t rowoff[TI], coloff[TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    const unsigned m = (unsigned)(mb + wm + 16 * i + r16);
-    rowoff[i] = hmc ? ((int64_t)(m / tokens) * g.c_heads * tokens + m % tokens) * cdim : (int64_t)m * g.N;
-  }
-#pragma unroll
-  for (int j = 0; j < TJ; ++j) {
-    const unsigned n0 = (unsigned)(nb + wn + 16 * j + 4 * kq);
-    const unsigned p = n0 / hd, r = n0 - p * hd, h = r / cdim;
-    coloff[j] = hmc ? ((int64_t)p * img * g.c_heads * tokens + (int64_t)h * tokens) * cdim + (r - h * cdim) : n0;
-  }
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    const int m = mb + wm + 16 * i + r16;
-    if (m >= g.M) continue;
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const int n0 = nb + wn + 16 * j + 4 * kq;
-      const int64_t off = rowoff[i] + coloff[j];
-      float x[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-      if constexpr (LN != 0) {
-        const int lr = wm + 16 * i + r16, lc = wn + 16 * j + 4 * kq;
-        const float mu = lnst[2 * lr], rs = lnst[2 * lr + 1];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = rs * (x[e] - mu * lncs[lc + e]);
-      }
-      if (g.ksplit == 1 && g.bias) {
-        const f4 bv = *reinterpret_cast<const f4*>(g.bias + n0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] += bv[e];
-      }
-      if (g.ksplit == 1 && g.res) {  // (row-major C)
-        float rv[4];
-        load4(g.res, cdt, off, rv);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] += rv[e];
-      }
-      store_n<4>(C, cdt, off, x);
-    }
-  }
-}
-
 // C = sum over the ksplit float32 partial products, converted to C's dtype;
 // 4 elements per thread.
 __global__ void __launch_bounds__(256) ksplit_reduce_kernel(const float* part, void* C, int64_t n4, int ksplit,
@@ -449,11 +59,11 @@ __global__ void __launch_bounds__(256) ksplit_reduce_kernel(const float* part, v
 // tile's (kFH + 2) x (kFW + 2)-token halo of X (rows outside the image are
 // zero) by the kFN rows of W_v, and the tile's own tokens (each tile row is a
 // run of 16 consecutive halo rows) by the kFN rows of W_g, with the load ring,
-// LDS swizzle and C^T accumulator layout of gemm_nt_kernel. The epilogue
+// LDS swizzle and C^T accumulator layout of gemm_ring_kernel. The epilogue
 // rounds both products to fp16 into the LDS the K loop used and forms the
 // gated convolution there: G and V never leave the chip, and the halo's extra
 // V rows are the price (180 V rows per 128 tokens). One-dimensional grid of
-// tiles * (hidden / kFN) work-groups; as in gemm_nt_kernel each XCD takes a
+// tiles * (hidden / kFN) work-groups; as in gemm_ring_kernel each XCD takes a
 // contiguous range of the order (tile, channel block), channel blocks
 // fastest, so the work-groups that read the same X halo share one XCD's L2.
 // (Measured at 40x40 tokens, one image, us per SwiGLU call: GTR-L 34.4, GTR-X
@@ -674,38 +284,81 @@ __global__ void __launch_bounds__(256) gated_conv_kernel(GatedConvArgs f) {
   }
 }
 
-// Both products on gemm_nt_kernel (the Spatial SwiGLU's output product and
-// gtr_gemm) use 64 x 64 work-group tiles (4 waves of 32 x 32). The K loop of a
-// work-group is a chain of dependent steps, so at the token counts of one or a
-// few images the number of work-groups sets the time more than the operand
-// reuse of a larger tile. Measured at one 40x40 image (us): the output product
-// 1600 x 384 x 1536 alone 10.3 with 64 x 64 tiles (150 work-groups) against
-// 15.1 with 128 x 64 (78); the whole Spatial SwiGLU 27.3 against 30.4 (128 x 64
-// tiles with K split in 2 and the reduction) at GTR-L and 40.5 against 41.3 at
-// GTR-X; 32 x 64 tiles 28.9 / 42.2; at 3200 and 12800 tokens the two tile
-// sizes are on par. K is split into the fewest slices that give 64 work-groups
-// when M x d alone does not (small grids only): every slice costs a float32
-// partial product and its share of the reduction. (With 8-wave tiles below 256
-// tiles, a target of 64 against 128 took the GTR-S block from 48.9 to 47.3 us:
-// its 75-tile output product no longer splits; 256 was slower at every width.)
-constexpr int kGemmBM = 64, kGemmBN = 64;
+// ---------------------------------------------------------------------------
+// Tile of a product (gemm_ring_kernel). The CUs run in lockstep through
+// ceil(tiles / CUs) tiles each, so the time goes with that count times the
+// tile's area; per area a larger tile is faster, as it reads fewer operand
+// bytes per product. Measured per area against 128 x 192 (us at 12800 x 384 x
+// 2304: 128 x 192 36, 64 x 192 39, 64 x 128 39, 64 x 64 45; 12800 x 1920 x 384: 36,
+// 43, 43, 46): the weights below. Where the larger tile leaves CUs idle the
+// smaller one wins, as the rule says: 8300 x 384 x 1536 20.1 in 64 x 128 (390
+// tiles) against 25.3 in 128 x 192 (130); 1600 x 384 x 1536 9.7 in 64 x 64 (150)
+// against 14.2 in 64 x 128 (75); with LN 1600 x 1920 x 384 10.6 in 64 x 192 (250)
+// against 11.4 in 64 x 64 (750), 1600 x 960 x 192 6.9 in 64 x 64 (375) against 8.0 in
+// 64 x 192 (125). All widths that no wider tile divides run in 64 x 64.
+// ---------------------------------------------------------------------------
+constexpr int kCUs = 256;
+constexpr int kGemmBM = 64, kGemmBN = 64;  // the smallest tile
+struct GemmTile {
+  int bm, bn;
+  float weight;
+};
+constexpr GemmTile kGemmTiles[] = {{128, 192, 1.f}, {64, 192, 1.05f}, {64, 128, 1.15f}, {64, 64, 1.25f}};
 
-// A grid of fewer tiles than the chip's 256 compute units leaves CUs idle, and
-// each work-group's K loop is a chain of dependent steps: there, 8 waves per
-// tile (the two 32-deep halves of every K step on separate waves, their sums
-// joined through LDS at the end) run the chain faster. Larger grids keep 4
-// waves per tile. Measured (us): 1600 x 384 x 1536 (150 tiles) 9.5 against
-// 10.1, 1600 x 384 x 384 5.0 against 5.3, the Spatial SwiGLU 26.4 / 38.5
-// against 27.2 / 40.6 (GTR-L / GTR-X); 1600 x 1920 x 384 (750 tiles) 10.8
-// against 9.3, 12800 x 384 x 1536 37.4 against 36.5.
-constexpr int kKHalvesBelow = 256;
-template <int ADT, int BDT, int MT, int LN>
-static void launch_gemm(const GemmArgs& g, unsigned tiles, hipStream_t stream) {
-  if (tiles < (unsigned)kKHalvesBelow)
-    hipLaunchKernelGGL((gemm_nt_kernel<ADT, BDT, MT, kGemmBM, kGemmBN, 2, LN>), dim3(tiles), dim3(512), 0, stream, g);
-  else
-    hipLaunchKernelGGL((gemm_nt_kernel<ADT, BDT, MT, kGemmBM, kGemmBN, 1, LN>), dim3(tiles), dim3(256), 0, stream, g);
+static int pick_tile(int64_t M, int N, bool ln) {
+  int best = 3;
+  float cost = 0.f;
+  for (int i = 3; i >= 0; --i) {
+    const GemmTile& t = kGemmTiles[i];
+    if (N % t.bn || (ln && i == 2)) continue;
+    const int64_t tiles = (M + t.bm - 1) / t.bm * (N / t.bn);
+    const float c = (float)((tiles + kCUs - 1) / kCUs) * t.bm * t.bn * t.weight;
+    if (i == 3 || c < cost) best = i, cost = c;
+  }
+  return best;
 }
+
+template <int ADT, int BDT, int MT, int BM, int BN, int WM, int WN, int S, int LN>
+static void launch_tile(const GemmArgs& g, hipStream_t stream) {
+  const int64_t wgs = (int64_t)((g.M + BM - 1) / BM) * ((g.N / BN + g.cols - 1) / g.cols) * g.ksplit;
+  hipLaunchKernelGGL((gemm_ring_kernel<ADT, BDT, MT, BM, BN, WM, WN, S, LN>), dim3((unsigned)wgs), dim3(64 * WM * WN), 0,
+                     stream, g);
+}
+
+// Column tiles per work-group of the row-normalised product in wide tiles: the
+// statistics of a row block cost about half a tile, once per work-group, and
+// two work-groups share a CU, so the time goes with max(1, work-groups / (2
+// CUs)) (cols + 1/2). Measured (us): 12800 x 1920 x 384 47 with one column tile,
+// 43.5 with two (500 work-groups), 51 with three; 8300 x 1920 x 384 35.4, 36.7, 46.
+static int pick_cols(int64_t M, int N, const GemmTile& t) {
+  const int64_t rows = (M + t.bm - 1) / t.bm, ntile = N / t.bn;
+  int best = 1;
+  float cost = 0.f;
+  for (int c = 1; c <= 4 && c <= ntile; ++c) {
+    const float rounds = (float)(rows * ((ntile + c - 1) / c)) / (2 * kCUs);
+    const float x = (rounds > 1.f ? rounds : 1.f) * (c + 0.5f);
+    if (c == 1 || x < cost) best = c, cost = x;
+  }
+  return best;
+}
+
+template <int ADT, int BDT, int MT, bool LN>
+static void launch_gemm(GemmArgs g, hipStream_t stream) {
+  const int t = g.ksplit > 1 ? 3 : pick_tile(g.M, g.N, LN);
+  g.cols = LN && t < 2 ? pick_cols(g.M, g.N, kGemmTiles[t]) : 1;
+  if (t == 0)
+    launch_tile<ADT, BDT, MT, 128, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
+  else if (t == 1)
+    launch_tile<ADT, BDT, MT, 64, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
+  else if (!LN && t == 2)
+    launch_tile<ADT, BDT, MT, 64, 128, 2, 2, 2, 0>(g, stream);
+  else
+    launch_tile<ADT, BDT, MT, 64, 64, 2, 2, LN ? 2 : 3, LN ? 1 : 0>(g, stream);
+}
+
+// K is split into the fewest slices that give 64 work-groups when M x d alone
+// does not (small grids only): every slice costs a float32 partial product and
+// its share of the reduction.
 static int out_ksplit(int64_t M, int d, int hidden) {
   const int64_t wgs = ((M + kGemmBM - 1) / kGemmBM) * (d / kGemmBN);
   int s = 1;
@@ -811,11 +464,10 @@ extern "C" gtr_status gtr_spatial_swiglu(const gtr_swiglu_args* a, hipStream_t s
   const int ks = out_ksplit(M, a->d, a->hidden);
   float* part = reinterpret_cast<float*>(ws + lay.part_off);
   GemmArgs g3{Hb, a->w_out, a->y, part, (int)M, a->d, a->hidden, a->y_dtype, ks, nullptr, ks == 1 ? a->residual : nullptr};
-  const unsigned tiles3 = (unsigned)(((M + kGemmBM - 1) / kGemmBM) * (a->d / kGemmBN) * ks);
   if (bf)
-    launch_gemm<GTR_F16, GTR_BF16, GTR_F16, 0>(g3, tiles3, stream);
+    launch_gemm<GTR_F16, GTR_BF16, GTR_F16, false>(g3, stream);
   else
-    launch_gemm<GTR_F16, GTR_F16, GTR_F16, 0>(g3, tiles3, stream);
+    launch_gemm<GTR_F16, GTR_F16, GTR_F16, false>(g3, stream);
   if (hipGetLastError() != hipSuccess) return GTR_ERR_HIP;
   if (ks > 1) {
     const int64_t n4 = M * a->d / 4;
@@ -826,7 +478,7 @@ extern "C" gtr_status gtr_spatial_swiglu(const gtr_swiglu_args* a, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// gtr_gemm: C = A B^T (+ bias) (+ res) on gemm_nt_kernel, 64 x 64 tiles, no
+// gtr_gemm: C = A B^T (+ bias) (+ res) on gemm_ring_kernel, 64 x 64 tiles, no
 // K split (the block's products have K = d or 64).
 // ---------------------------------------------------------------------------
 static gtr_status gemm_check(const gtr_gemm_args* a) {
@@ -868,18 +520,17 @@ extern "C" gtr_status gtr_gemm(const gtr_gemm_args* a, hipStream_t stream) {
   if (st != GTR_OK) return st;
   GemmArgs g{a->a, a->b, a->c, nullptr, (int)a->M, a->N, a->K, (int)a->c_dtype, 1, a->bias, a->res,
              a->a_tokens, a->c_tokens, a->c_tokens ? a->c_heads : 0, a->c_tokens ? a->c_head_dim : 0,
-             a->row_norm ? a->row_norm_eps : 0.f, 0};
-  const unsigned tiles = (unsigned)(((a->M + kGemmBM - 1) / kGemmBM) * (a->N / kGemmBN));
+             a->row_norm ? a->row_norm_eps : 0.f, 1};
   if (a->a_dtype == GTR_BF16) {
     if (a->row_norm)
-      launch_gemm<GTR_BF16, GTR_BF16, GTR_BF16, 1>(g, tiles, stream);
+      launch_gemm<GTR_BF16, GTR_BF16, GTR_BF16, true>(g, stream);
     else
-      launch_gemm<GTR_BF16, GTR_BF16, GTR_BF16, 0>(g, tiles, stream);
+      launch_gemm<GTR_BF16, GTR_BF16, GTR_BF16, false>(g, stream);
   } else {
     if (a->row_norm)
-      launch_gemm<GTR_F16, GTR_F16, GTR_F16, 1>(g, tiles, stream);
+      launch_gemm<GTR_F16, GTR_F16, GTR_F16, true>(g, stream);
     else
-      launch_gemm<GTR_F16, GTR_F16, GTR_F16, 0>(g, tiles, stream);
+      launch_gemm<GTR_F16, GTR_F16, GTR_F16, false>(g, stream);
   }
   return hipGetLastError() == hipSuccess ? GTR_OK : GTR_ERR_HIP;
 }

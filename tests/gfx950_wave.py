@@ -1662,6 +1662,20 @@ def gload(nregs, nbytes=None):
     return h
 
 
+def gload_lds(nregs):
+    """A load straight to LDS: lane l's bytes go to M0 + offset + 4 nregs l."""
+    def h(w, i):
+        saddr = i.ops[1] if len(i.ops) > 1 else 'off'
+        lanes = w.active()
+        a, d, o = gaddr(w, i, i.ops[0], saddr)
+        w.check_addr(i, a, d, o, 4 * nregs, 'r', lanes)
+        m0, mo, md = w.s32('m0', i)
+        to = VVal((np.uint32(m0) + np.arange(NL, dtype=np.uint32) * np.uint32(4 * nregs)).astype(np.uint32),
+                  np.full(NL, bool(md)), np.full(NL, bool(mo)))
+        lds_check(w, i, to, [int(i.mods.get('offset', 0))], 4 * nregs, lanes)
+    return h
+
+
 def gstore(nregs, nbytes=None):
     def h(w, i):
         vaddr, data = i.ops[0], i.ops[1]
@@ -1755,6 +1769,7 @@ def buffer_op(nregs, store):
     return h
 
 
+HANDLERS.update({'global_load_lds_dwordx4': gload_lds(4)})
 HANDLERS.update({'buffer_load_dword': buffer_op(1, False), 'buffer_load_dwordx2': buffer_op(2, False),
                  'buffer_load_dwordx4': buffer_op(4, False),
                  'buffer_store_dword': buffer_op(1, True), 'buffer_store_dwordx2': buffer_op(2, True),

@@ -92,7 +92,30 @@ def test_gemm_row_norm(dtype, M, N, K, offset):
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
-@pytest.mark.parametrize("B,L,heads,parts", [(1, 1600, 6, 4), (2, 207, 3, 1)])
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("M,N,K", [(1, 192, 64), (65, 384, 128), (63, 128, 192),        # one row, one to three K steps
+                                   (4097, 1920, 192), (12801, 1920, 64), (3300, 960, 192),  # 128- and 64-row tiles of 192
+                                   (8300, 384, 448), (16390, 128, 64), (20000, 64, 128)])  # 128- and 64-column tiles
+def test_gemm_tiles(dtype, norm, M, N, K):
+    """gtr_gemm at row counts that no tile divides, over every tile of the
+    dispatch, with one to seven K steps, against a float64 product (and layer
+    normalisation). The result is rounded once (half an ulp of it) after float32
+    sums of K products, each with the operands' exact values: 2^-24 sqrt(K) of
+    the largest terms, far inside the 1e-3 of the largest result."""
+    rng = np.random.default_rng(M + N + K)
+    a, b = rnd(rng, M, K, dtype=dtype), rnd(rng, N, K, std=K ** -0.5, dtype=dtype)
+    bi = rnd(rng, N, dtype=torch.float32)
+    c = gtr.gtr_gemm(a.to(DEV), b.to(DEV), bias=bi.to(DEV), row_norm_eps=1e-6 if norm else None)
+    torch.cuda.synchronize()
+    x = a.double().numpy()
+    want = (oracle.layer_norm(x, None, None, 1e-6) if norm else x) @ b.double().numpy().T + bi.double().numpy()
+    ulp = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -11
+    err = np.max(np.abs(c.double().cpu().numpy() - want) / (np.abs(want) * ulp + 1e-3 * np.max(np.abs(want))))
+    assert err <= 1.0, err
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("B,L,heads,parts", [(1, 1600, 6, 4), (2, 207, 3, 1), (3, 1433, 6, 5)])
 def test_gemm_head_major_operands(dtype, B, L, heads, parts):
     """gtr_gemm storing c head-major and reading a head-major a: the same
     products, placed as a reshape and transpose of the row-major ones."""

@@ -435,7 +435,7 @@ def swiglu_asm() -> str:
     from paper_2609_26590_amd import build as b
     src = os.path.join(CSRC, "swiglu.hip")
     h = hashlib.sha256()
-    for f in ("swiglu.hip", "gtr_device.h", "gtr_internal.h"):
+    for f in ("swiglu.hip", "gemm.h", "gtr_device.h", "gtr_internal.h"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     with open(os.path.join(ROOT, "include", "gtr.h"), "rb") as fh:
@@ -476,7 +476,7 @@ def check_kernel(text, name, kern, regions, wgs, waves=4):
                                                             (1, 1, 1, 64, 1600, 1536, 384, 1, 1, 8),
                                                             (1, 1, 1, 64, 3200, 384, 384, 1, 1, 6),
                                                             (2, 2, 2, 64, 414, 384, 64, 2, 1, 9),
-                                                            # 4 waves per tile at 256 tiles and more
+                                                            # wide tiles: remainders of 64- and 128-row tiles
                                                             (2, 2, 2, 64, 3200, 384, 64, 2, 1, 1),
                                                             (1, 2, 1, 64, 4096, 384, 128, 0, 1, 0),
                                                             # rows of A normalised (the block's first layer norm)
@@ -500,27 +500,39 @@ def test_swiglu_gemm_addresses(adt, bdt, mt, bn, M, N, K, cdt, ks, epi):
     ct = (M // 2 if M % 2 == 0 else M) if epi & 8 else 0
     kern = struct.pack("<QQQQiiiii4xQQqqiifi", A, B, C, P, M, N, K, cdt, ks, BI if epi & 1 else 0,
                        R if epi & 2 else 0, at, ct, 6 if ct else 0, 64 if ct else 0, 1e-6 if epi & 16 else 0.0, 0)
-    # 8 waves per tile below 256 tiles (the K halves on separate waves), 4 above
-    kw = 2 if ((M + 63) // 64) * (N // bn) * ks < 256 else 1
-    name = f"_ZN3gtr14gemm_nt_kernelILi{adt}ELi{bdt}ELi{mt}ELi64ELi{bn}ELi{kw}ELi{1 if epi & 16 else 0}EEEvNS_8GemmArgsE"
-    assert name in emu.kernel_names(text)
-    gx, gy = (M + 63) // 64, N // bn
-    T = gx * gy * ks
+    # every tile that divides N (K slices: the 64 x 64 one), each kernel of the row normalisation, and
+    # work-groups of two column tiles
+    seen = 0
+    for bm, tn, wm, wn in ((128, 192, 2, 4), (64, 192, 2, 4), (64, 128, 2, 2), (64, 64, 2, 2)):
+        if N % tn or (ks > 1 and tn != 64):
+            continue
+        names = [n for n in emu.kernel_names(text) if "gemm_ring_kernel" in n and
+                 f"ILi{adt}ELi{bdt}ELi{mt}ELi{bm}ELi{tn}ELi{wm}ELi{wn}E" in n]
+        for name in names:
+            ln = int(re.search(r"ELi(\d)EEEv", name).group(1))
+            if (ln > 0) != bool(epi & 16):
+                continue
+            seen += 1
+            for cols in (1, 2) if ks == 1 and ln != 1 and N // tn > 1 else (1,):
+                gx, gy = (M + bm - 1) // bm, (N // tn + cols - 1) // cols
+                T = gx * gy * ks
 
-    def block_of(x, y, z):
-        """The 1-D block id whose tile is (x, y, z): XCD k = b % 8 runs tile
-        positions k (T // 8) + min(k, T % 8) + b // 8, column blocks fastest."""
-        j = (z * gx + x) * gy + y
-        for k in range(8):
-            start, count = k * (T // 8) + min(k, T % 8), (T - k + 7) // 8
-            if start <= j < start + count:
-                return (j - start) * 8 + k
-        raise AssertionError(j)
+                def block_of(x, y, z):
+                    """The 1-D block id whose tile group is (x, y, z): XCD k = b % 8 runs the positions
+                    k (T // 8) + min(k, T % 8) + b // 8, column groups fastest."""
+                    j = (z * gx + x) * gy + y
+                    for k in range(8):
+                        start, count = k * (T // 8) + min(k, T % 8), (T - k + 7) // 8
+                        if start <= j < start + count:
+                            return (j - start) * 8 + k
+                    raise AssertionError(j)
 
-    ids = sorted({block_of(x, y, z) for x in sorted({0, gx - 1}) for y in sorted({0, gy - 1})
-                  for z in sorted({0, ks - 1})})
-    assert all(0 <= b < T for b in ids)
-    check_kernel(text, name, kern, regions, [(b, 0, 0) for b in ids], waves=4 * kw)
+                ids = sorted({block_of(x, y, z) for x in sorted({0, gx - 1}) for y in sorted({0, gy - 1})
+                              for z in sorted({0, ks - 1})})
+                assert all(0 <= b < T for b in ids)
+                check_kernel(text, name, kern[:-4] + struct.pack("<i", cols), regions, [(b, 0, 0) for b in ids],
+                             waves=wm * wn)
+    assert seen > 0
 
 
 @pytest.mark.parametrize("dt,B,H,W,d,hidden", [(1, 2, 7, 9, 64, 128), (2, 1, 40, 40, 384, 192),
