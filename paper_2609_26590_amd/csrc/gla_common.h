@@ -182,8 +182,10 @@ __device__ __forceinline__ float gexp(float x) {
 // factor e / (u - 1) undoes the rounding of u (u - 1 is exact), which keeps the
 // result within a few ulp with one log and one reciprocal.
 // Hardware log2 and reciprocal (about 1 ulp each); when u rounds to 1 the
-// quotient is not used (a select, not a branch).
-__device__ __forceinline__ float log_decay(const GlaParams& P, float x) {
+// quotient is not used (a select, not a branch). `inv_tau` is P.inv_tau, or 0
+// for a position past the end of the sequence: the zero it reads is a logit,
+// and its log-decay must be 0 (the state after the last token passes it).
+__device__ __forceinline__ float log_decay(const GlaParams& P, float x, float inv_tau) {
   if (P.gkind != GTR_GATE_LOGITS) return x;
   constexpr float kLn2 = 0.693147180559945309f;
   const float e = __expf(-fabsf(x));
@@ -191,7 +193,7 @@ __device__ __forceinline__ float log_decay(const GlaParams& P, float x) {
   const float d = u - 1.f;
   const float r = __builtin_amdgcn_logf(u) * kLn2 * e * __builtin_amdgcn_rcpf(d);
   const float l1p = d == 0.f ? e : r;
-  return (fminf(x, 0.f) - l1p) * P.inv_tau;
+  return (fminf(x, 0.f) - l1p) * inv_tau;
 }
 
 // Maximum over the groups of N consecutive lanes (N = 4 or 8) with DPP

@@ -226,7 +226,7 @@ struct Chunk {
       cvt_raw(rk[s], IN, kx);
       cvt_raw(rg[s], P.gdt, gx);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e]);
+      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e], valid ? P.inv_tau : 0.f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         // local inclusive cumulative sum over the 16 tokens of this sub-chunk
@@ -396,7 +396,7 @@ struct Chunk {
       cvt_raw(rk, IN, kx[s]);
       cvt_raw(rg, P.gdt, gx);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e]);
+      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e], valid ? P.inv_tau : 0.f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) ax[s][e] = row_inclusive_scan(gx[e]);
     }

@@ -161,7 +161,7 @@ struct Lean {
       cvt_raw(rg[s], P.gdt, gx);
       if (P.gkind == GTR_GATE_LOGITS) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e]);
+        for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e], valid ? P.inv_tau : 0.f);
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -331,7 +331,7 @@ struct Lean {
       cvt_raw(rk, IN, kx[s]);
       cvt_raw(rg, P.gdt, gx);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e]);
+      for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e], valid ? P.inv_tau : 0.f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) ax[s][e] = row_inclusive_scan(gx[e]);
     }

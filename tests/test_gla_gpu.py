@@ -446,6 +446,28 @@ def test_fusions_parity(gtr, case, path):
         assert rel_err(sf, sf_ref) <= tol_for(wl.dtype, "f32")
 
 
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("dtype,chunk", [("f16", 64), ("bf16", 32), ("f32", 64), ("f16", 128)])
+def test_gate_logits_ragged_final_state(gtr, dtype, chunk, path):
+    """S_final with gate logits and a last chunk that the sequence does not
+    fill: the positions past its end must not decay the state (a zero logit is
+    not a zero log-decay)."""
+    wl = Workload("ragged", B=1, heads=2, H=9, W=15, dk=64, dv=64, dtype=dtype, odtype="f32", gate_mu=2.0,
+                  gate_std=1.0, qk_std=0.125, v_std=1.0, s0_std=0.1, want_final=True, chunk=chunk, seed=77)
+    inp = make_inputs(wl)
+    a = torch.from_numpy(np.random.default_rng(77).normal(1.0, 1.0, size=tuple(inp["g"].shape))).float()
+    a = a.to(torch_dtype(dtype))
+    dev = torch.device("cuda")
+    q, k, v = (inp[n].to(dev) for n in ("q", "k", "v"))
+    o, sf = call(gtr, q, k, v, a.to(dev), H=wl.H, W=wl.W, scale=wl.scale, chunk=chunk, scan="col", s0=inp["s0"].to(dev),
+                 want_final=True, o_dtype=torch.float32, path=path, gate_tau=4.0)
+    torch.cuda.synchronize()
+    o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], oracle.log_decay_from_logits(a, 4.0), inp["s0"],
+                               scale=wl.scale, H=wl.H, W=wl.W, scan="col")
+    assert rel_err(o, o_ref) <= tol_for(dtype, "f32")
+    assert rel_err(sf, sf_ref) <= tol_for(dtype, "f32")
+
+
 def test_epilogue_leaves_the_state_alone(gtr):
     """The epilogue changes what is written to o, never the recurrence: S_final
     is the same with and without it."""
