@@ -73,7 +73,27 @@ struct GlaParams {
   int nxcd;     // one launch, 16-bit kernel: XCDs of the sequence-per-XCD grid (0: plain chunk-major grid)
   unsigned spin;  // polls of a bounded wait
   int group;      // one launch, 16-bit kernel: grouped look-back (kGroup chunks per group)
+  unsigned hrec;  // min(floor(2^32 / H), 2^32 - 1): division by H of the column scans
 };
+
+// Spatial index of scan position `pos` < L (scan_to_spatial in 32 bits: the
+// host keeps a sequence's rows below 2 GB, so L < 2^25). The quotient from the
+// reciprocal is the true one or one less. (The 64-bit division of the column
+// scans took about 100 of a wave's 1,400 vector instructions, two to three
+// times per wave: op at 128 x 128 tokens, d_k 32, 4 images, column scan.)
+__device__ __forceinline__ unsigned scan_token(const GlaParams& P, unsigned pos) {
+  const unsigned H = (unsigned)P.H, W = (unsigned)P.W;
+  if (P.scan == GTR_SCAN_ROW_REV || P.scan == GTR_SCAN_COL_REV) pos = H * W - 1u - pos;
+  if (P.scan == GTR_SCAN_COL || P.scan == GTR_SCAN_COL_REV) {
+    unsigned j = __umulhi(pos, P.hrec), i = pos - j * H;
+    if (i >= H) {
+      i -= H;
+      ++j;
+    }
+    return i * W + j;
+  }
+  return pos;
+}
 
 constexpr int tile_threads(int chunk) { return chunk / 16 * kWave; }
 

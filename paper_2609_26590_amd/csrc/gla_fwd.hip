@@ -166,9 +166,9 @@ struct Chunk {
 
   // Spatial token index of scan position `pos` (0 past the end) and whether
   // the position exists.
-  static __device__ __forceinline__ int64_t token(const GlaParams& P, int64_t pos, bool& valid) {
-    valid = pos < P.L;
-    return valid ? scan_to_spatial(pos, P.H, P.W, P.scan) : 0;
+  static __device__ __forceinline__ unsigned token(const GlaParams& P, unsigned pos, bool& valid) {
+    valid = pos < (unsigned)P.L;
+    return valid ? scan_token(P, pos) : 0u;
   }
 
   // Loads and per-token work. Writes v^T, the sub-chunk totals, the per-wave
@@ -178,7 +178,7 @@ struct Chunk {
   __device__ __forceinline__ void load(const GlaParams& P, S& sm, int bh, int c) {
     lanes();
     bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
 
     // issue every load before converting any of them; a position past the end
     // of the sequence reads zeros through the descriptors' range check
@@ -196,14 +196,14 @@ struct Chunk {
     Raw rq[KS], rk[KS], rg[KS], rv[VS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const uint32_t e = (uint32_t)t * DK + 32 * s + 8 * gq;
+      const uint32_t e = t * DK + 32 * s + 8 * gq;
       ld_raw_buf(qr, IN, valid ? e * ES : kOutOfRange, rq[s]);
       ld_raw_buf(kr, IN, valid ? e * ES : kOutOfRange, rk[s]);
       ld_raw_buf(gr, P.gdt, valid ? e * gs : kOutOfRange, rg[s]);
     }
 #pragma unroll
     for (int s = 0; s < VS; ++s)
-      ld_raw_buf(vr, IN, valid ? ((uint32_t)t * P.dvp + 32 * s + 8 * gq) * ES : kOutOfRange, rv[s]);
+      ld_raw_buf(vr, IN, valid ? (t * P.dvp + 32 * s + 8 * gq) * ES : kOutOfRange, rv[s]);
 
     // v^T tile
     float vmax = 0.f;
@@ -379,7 +379,7 @@ struct Chunk {
   // rolled to keep the code small.
   __device__ __forceinline__ f4 exact_diagonal(const GlaParams& P, float (*pt)[17], int bh, int c) {
     bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
     const int64_t kb = ((int64_t)bh * P.L + t) * DK;
     float qx[KS][8], kx[KS][8], ax[KS][8];
 #pragma unroll
@@ -613,7 +613,7 @@ struct Chunk {
       const int idx = threadIdx.x + it * NT;
       const int rr = idx / PIECES, pc = idx % PIECES;
       bool valid;
-      const int64_t t = token(P, (int64_t)c * C + rr, valid);
+      const unsigned t = token(P, (unsigned)(c * C) + rr, valid);
       ld_raw(P.gate, P.gatedt, ((int64_t)bh * P.L + t) * P.dvp + 8 * pc, rz[it]);
     }
   }
@@ -639,7 +639,7 @@ struct Chunk {
       const int idx = threadIdx.x + it * NT;
       const int rr = idx / PIECES, pc = idx % PIECES;
       bool valid;
-      const int64_t t = token(P, (int64_t)c * C + rr, valid);
+      const unsigned t = token(P, (unsigned)(c * C) + rr, valid);
       const int64_t off = ((int64_t)bh * P.L + t) * P.dvp + 8 * pc;  // token 0 past the end: in bounds
       float x[8];
 #pragma unroll
@@ -1254,6 +1254,7 @@ static gtr_status gla_launch(const gtr_gla_args* a, const GlaShape& s, hipStream
   P.nxcd = pl.nxcd;
   P.spin = a->spin_limit ? a->spin_limit : kSpinDefault;
   P.group = pl.group;
+  P.hrec = a->H > 1 ? (unsigned)(((uint64_t)1 << 32) / (unsigned)a->H) : 0xffffffffu;
 
   void* kargs[] = {&P};
   hipError_t err;

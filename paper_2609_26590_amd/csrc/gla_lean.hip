@@ -89,6 +89,8 @@ struct Lean {
   };
 
   int w, lane, tr, g, r;
+  unsigned tok;      // spatial index of this lane's token (0 past the end of the sequence)
+  bool tok_ok;       // the position exists
   float qh[KS][8];   // q 2^(a_r)
   float ke[KS][8];   // k 2^(T_R - a_r)
   h8 qt[KS];         // q 2^(A_r), the readout operand
@@ -113,9 +115,9 @@ struct Lean {
     r = 16 * w + tr;
   }
 
-  static __device__ __forceinline__ int64_t token(const GlaParams& P, int64_t pos, bool& valid) {
-    valid = pos < P.L;
-    return valid ? scan_to_spatial(pos, P.H, P.W, P.scan) : 0;
+  static __device__ __forceinline__ unsigned token(const GlaParams& P, unsigned pos, bool& valid) {
+    valid = pos < (unsigned)P.L;
+    return valid ? scan_token(P, pos) : 0u;
   }
 
   // LDS address for the transposing read that gives lane (g, i) the column
@@ -129,8 +131,9 @@ struct Lean {
   template <class S>
   __device__ __forceinline__ void load(const GlaParams& P, S& sm, int bh, int c) {
     lanes();
-    bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+    tok = token(P, (unsigned)(c * C) + r, tok_ok);
+    const unsigned t = tok;
+    const bool valid = tok_ok;
     const uint32_t gs = P.gdt == GTR_F32 ? 4 : 2;
     const int64_t L = P.L;
     const char* qb = static_cast<const char*>(P.q) + (int64_t)bh * L * DK * 2;
@@ -143,14 +146,14 @@ struct Lean {
     const __amdgpu_buffer_rsrc_t gr = make_rsrc(gb, (uint32_t)(L * DK * gs));
     Raw rq[KS], rk[KS], rg[KS], rv[VS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(gr, P.gdt, valid ? ((uint32_t)t * DK + 32 * s + 8 * g) * gs : kOutOfRange, rg[s]);
+    for (int s = 0; s < KS; ++s) ld_raw_buf(gr, P.gdt, valid ? (t * DK + 32 * s + 8 * g) * gs : kOutOfRange, rg[s]);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(kr, IN, valid ? ((uint32_t)t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rk[s]);
+    for (int s = 0; s < KS; ++s) ld_raw_buf(kr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rk[s]);
 #pragma unroll
     for (int s = 0; s < VS; ++s)
-      ld_raw_buf(vr, IN, valid ? ((uint32_t)t * P.dvp + 32 * s + 8 * g) * 2 : kOutOfRange, rv[s]);
+      ld_raw_buf(vr, IN, valid ? (t * P.dvp + 32 * s + 8 * g) * 2 : kOutOfRange, rv[s]);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(qr, IN, valid ? ((uint32_t)t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rq[s]);
+    for (int s = 0; s < KS; ++s) ld_raw_buf(qr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rq[s]);
 
     // log2-decays and their inclusive sums within the sub-chunk
     float a[KS][8], tot[KS][8];
@@ -313,8 +316,8 @@ struct Lean {
   // mid-point factors: P^T[j][r] = sum_d q_r k_j exp(a_r - a_j), j <= r, from
   // the raw q, k, g of the sub-chunk (reloaded; rare).
   __device__ __forceinline__ f4 exact_diagonal(const GlaParams& P, float (*pt)[17], int bh, int c) const {
-    bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+    const unsigned t = tok;
+    const bool valid = tok_ok;
     const int64_t kb = ((int64_t)bh * P.L + t) * DK;
     float qx[KS][8], kx[KS][8], ax[KS][8];
 #pragma unroll
@@ -542,9 +545,8 @@ struct Lean {
 
   // The output-gate pre-activation for this lane's row and columns (loaded
   // early, with the other inputs; only when P.gate is set).
-  __device__ __forceinline__ void prefetch_gate(const GlaParams& P, int bh, int c, Raw (&rz)[VB]) const {
-    bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+  __device__ __forceinline__ void prefetch_gate(const GlaParams& P, int bh, Raw (&rz)[VB]) const {
+    const unsigned t = tok;
 #pragma unroll
     for (int jb = 0; jb < VB; ++jb) {
       const int64_t off = ((int64_t)bh * P.L + t) * P.dvp + 16 * jb + 4 * g;
@@ -562,8 +564,8 @@ struct Lean {
   // columns per value block; `poison` stores NaN instead.
   __device__ __forceinline__ void store(const GlaParams& P, int bh, int c, const f4 (&O)[VB], const Raw (&rz)[VB],
                                         bool poison) const {
-    bool valid;
-    const int64_t t = token(P, (int64_t)c * C + r, valid);
+    const unsigned t = tok;
+    const bool valid = tok_ok;
     const float mul = poison ? __builtin_nanf("") : P.scale;
     float x[VB][4];
 #pragma unroll
@@ -715,7 +717,7 @@ gla_lean_kernel(GlaParams P) {
   // the output gate's loads overlap the exchange, the state tile and the
   // readout (issued earlier they would hold registers through every phase)
   Raw rz[T::VB];
-  if (P.gate) ch.prefetch_gate(P, bh, c, rz);
+  if (P.gate) ch.prefetch_gate(P, bh, rz);
   const bool okw = base >= -1;
   // one exchange makes the outcome uniform (a wait that ran out, or a NaN
   // state handed over by a poisoned chunk before it, poisons everything this

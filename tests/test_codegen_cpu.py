@@ -132,7 +132,7 @@ def test_emulator_bounds_a_data_dependent_buffer_offset_by_its_descriptor():
 # ---------------------------------------------------------------------------
 DT = {"f32": (0, 4), "f16": (1, 2), "bf16": (2, 2)}
 SCAN = {"row": 0, "col": 1, "row_rev": 2, "col_rev": 3}
-KERNARG_BYTES = 216  # sizeof(GlaParams)
+KERNARG_BYTES = 224  # sizeof(GlaParams)
 
 
 def a256(x):
@@ -232,11 +232,11 @@ def kernel_args(c: Shape, ln: Launch = Launch()):
     regions.insert(0, emu.Region("sync", ws + sync, ns * 16, "rw"))
     regions.insert(0, emu.Region("fault", ws, 256, "rw"))
     regions.append(emu.Region("kernarg", emu.KERNARG_BASE, KERNARG_BYTES, "r"))
-    kern = struct.pack("<7Q6iqifi4x6Qif2Qif6iIi", q, k, v, g, o, s0, sf, DT[c.dt][0], DT[c.gdt][0],
+    kern = struct.pack("<7Q6iqifi4x6Qif2Qif6iIiI4x", q, k, v, g, o, s0, sf, DT[c.dt][0], DT[c.gdt][0],
                        DT[c.odt][0], c.BH, c.H, c.W, c.L, c.NC, c.dk ** -0.5, SCAN[c.scan],
                        ws + agg, ws + rec, ws + states, ws + sync, ws + flags, ws,
                        1 if c.logits else 0, 1.0 / 16, z, nw, DT[c.zdt][0] if c.zdt else 0, 1e-5,
-                       c.dv, ln.vparts, ns, ln.desc, ln.publish, ln.nxcd, 8, ln.group)
+                       c.dv, ln.vparts, ns, ln.desc, ln.publish, ln.nxcd, 8, ln.group, min((1 << 32) // c.H, (1 << 32) - 1))
     assert len(kern) == KERNARG_BYTES
     return kern, regions
 

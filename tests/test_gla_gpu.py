@@ -468,6 +468,18 @@ def test_gate_logits_ragged_final_state(gtr, dtype, chunk, path):
     assert rel_err(sf, sf_ref) <= tol_for(dtype, "f32")
 
 
+@pytest.mark.parametrize("scan", ["col", "col_rev"])
+@pytest.mark.parametrize("H,W", [(1, 130), (130, 1), (3, 67), (67, 3), (1021, 2)])
+def test_column_scans_of_narrow_grids(gtr, H, W, scan):
+    """The column scans' division by H at its smallest and at prime sizes."""
+    wl = Workload("narrow", B=1, heads=1, H=H, W=W, dk=32, dv=64, dtype="f16", odtype="f32", gate_mu=2.0, gate_std=1.0,
+                  qk_std=0.2, v_std=1.0, chunk=64, seed=H * W)
+    o_ref, _ = _reference(wl, scan)
+    for path in PATHS:
+        o, _ = run_gpu(gtr, wl, scan, 64, path)
+        assert rel_err(o, o_ref) <= tol_for("f16", "f32"), path
+
+
 def test_epilogue_leaves_the_state_alone(gtr):
     """The epilogue changes what is written to o, never the recurrence: S_final
     is the same with and without it."""
