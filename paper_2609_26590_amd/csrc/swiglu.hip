@@ -23,14 +23,6 @@
 namespace gtr {
 
 constexpr int KB = 4;     // minimum 64-wide K-steps per slice when splitting K
-// LDS tiles: rows of 32 K elements (64 bytes, no padding); the 16-byte piece
-// c of row r sits at piece c ^ kSwz(r). Measured on gfx950, ds_read_b128 serves
-// 32 lanes per cycle from 32 distinct 16-byte slots (address / 16 mod 32) and
-// ds_write_b128 16 lanes from 16 slots (mod 16): with this swizzle the operand
-// reads (lanes = 16 rows x 2 pieces) and the staging writes (lanes = 4 rows x
-// 4 pieces) both hit distinct slots.
-constexpr int kPitch = 32;
-__device__ __forceinline__ int kSwz(int r) { return (r >> 2) & 2; }
 // C = sum over the ksplit float32 partial products, converted to C's dtype;
 // 4 elements per thread.
 __global__ void __launch_bounds__(256) ksplit_reduce_kernel(const float* part, void* C, int64_t n4, int ksplit,
@@ -56,29 +48,31 @@ __global__ void __launch_bounds__(256) ksplit_reduce_kernel(const float* part, v
 // H[b][t][c] = SiLU(G[b][t][c]) * (sum_{u,v} V[b][t + (u-1, v-1)][c] * cw[c][u][v] + cb[c]),
 // G = X W_g^T and V = X W_v^T, in one launch. A work-group owns a tile of
 // kFH x kFW tokens of one image and kFN channels. Its K loop multiplies the
-// tile's (kFH + 2) x (kFW + 2)-token halo of X (rows outside the image are
-// zero) by the kFN rows of W_v, and the tile's own tokens (each tile row is a
-// run of 16 consecutive halo rows) by the kFN rows of W_g, with the load ring,
-// LDS swizzle and C^T accumulator layout of gemm_ring_kernel. The epilogue
-// rounds both products to fp16 into the LDS the K loop used and forms the
-// gated convolution there: G and V never leave the chip, and the halo's extra
-// V rows are the price (180 V rows per 128 tokens). One-dimensional grid of
-// tiles * (hidden / kFN) work-groups; as in gemm_ring_kernel each XCD takes a
-// contiguous range of the order (tile, channel block), channel blocks
-// fastest, so the work-groups that read the same X halo share one XCD's L2.
-// (Measured at 40x40 tokens, one image, us per SwiGLU call: GTR-L 34.4, GTR-X
-// 45.9 with this order; 35.1 / 46.9 with channel blocks slowest; 34.2 / 46.6
-// with the plain two-dimensional grid.)
+// tile's (kFH + 2) x (kFW + 2)-token halo of X by the kFN rows of W_v, and the
+// tile's own tokens (each tile row is a run of 16 consecutive halo rows) by the
+// kFN rows of W_g, with the transfers to LDS, the swizzle and the C^T
+// accumulator layout of gemm_ring_kernel (two stages of 64-deep K steps, 80 KB:
+// two work-groups per CU). Halo rows outside the image read some row of it and
+// their V is zeroed. The epilogue rounds both products to fp16 into the LDS the
+// K loop used and forms the gated convolution there: G and V never leave the
+// chip, and the halo's extra V rows are the price (180 V rows per 128 tokens).
+// One-dimensional grid of tiles * (hidden / kFN) work-groups; as in
+// gemm_ring_kernel each XCD takes a contiguous range of the order (tile, channel
+// block), channel blocks fastest, so the work-groups that read the same X halo
+// share one XCD's L2. (Measured at 40x40 tokens, one image, us per SwiGLU call
+// with an earlier K loop: GTR-L 34.4, GTR-X 45.9 with this order; 35.1 / 46.9
+// with channel blocks slowest; 34.2 / 46.6 with the plain two-dimensional grid.)
 constexpr int kFH = 8, kFW = 16;         // tile: 8 rows of 16 tokens
 constexpr int kFHW = kFW + 2;            // halo row length
 constexpr int kFV = (kFH + 2) * kFHW;    // halo tokens (180)
-constexpr int kFVT = (kFV + 15) / 16;    // MFMA row blocks of V (12; rows 180..191 are zero padding)
+constexpr int kFVT = (kFV + 15) / 16;    // MFMA row blocks of V (12; rows 180..191 are padding)
 constexpr int kFN = 64;                  // channels per work-group
-constexpr int kFA = kFVT * 16 * 4 / 256; // 16-byte A pieces per thread per K step (3)
-constexpr int kFB = kFN * 4 * 2 / 256;   // 16-byte pieces of the W_g and W_v tiles per thread per K step
+constexpr int kFWaves = 8;               // 4 row groups x 2 halves of the channels
+constexpr int kFA = kFVT * 16 / 8 / kFWaves;  // transfers of the halo per wave per K step (3)
+constexpr int kFB = 2 * kFN / 8 / kFWaves;    // of W_g and W_v (2)
 constexpr int kFP = kFN / 8;             // 16-byte pieces (8 channels) of one token's kFN channels
-static_assert(kFB >= 1 && kFN * 4 * 2 % 256 == 0 && (kFP & (kFP - 1)) == 0, "weight tiles split evenly over 256 threads");
-static_assert(kFVT % 4 == 0 && kFH % 4 == 0, "row blocks split evenly over 4 waves");
+static_assert(kFN == 64 && kFWaves == 8 && kFH == 8 && kFW == 16, "wave and thread split");
+static_assert(kFVT * 2 % kFWaves == 0, "transfers split evenly over the waves");
 
 struct GatedConvArgs {
   const void* X;
@@ -92,16 +86,20 @@ struct GatedConvArgs {
 };
 
 template <int DT>
-__global__ void __launch_bounds__(256) gated_conv_kernel(GatedConvArgs f) {
+__global__ void __launch_bounds__(64 * kFWaves) __attribute__((amdgpu_waves_per_eu(4)))
+gated_conv_kernel(GatedConvArgs f) {
   typedef Operand<DT, DT> OP;
-  constexpr int SA = kFVT * 16 * kPitch, SB = kFN * kPitch;  // 16-bit elements per stage
-  constexpr int VT = kFVT / 4, GT = kFH / 4;                 // row blocks of V and G per wave
-  constexpr int NJ = kFN / 16;                               // column blocks (all waves)
-  static_assert(2 * (SA + 2 * SB) >= (kFVT * 16 + kFH * kFW) * kFN, "epilogue tiles fit the stage buffers");
-  __shared__ __attribute__((aligned(16))) unsigned short stg[2][SA + 2 * SB];
-  __shared__ __attribute__((aligned(16))) float wsm[kFN * 9 + kFN];
+  constexpr int NT = 64 * kFWaves;
+  constexpr int SA = kFVT * 16 * kPitch64, SB = kFN * kPitch64;  // 16-bit elements per stage: halo, each weight tile
+  constexpr int ST = SA + 2 * SB;
+  constexpr int VT = kFVT / 4, GT = kFH / 4;                     // row blocks of V and G per wave
+  constexpr int NJ = kFN / 32;                                   // column blocks per wave
+  constexpr int kTiles = (kFVT * 16 + kFH * kFW) * kFN;          // 16-bit elements of the epilogue's V and G
+  static_assert(2 * ST * 2 >= kTiles * 2 + (9 * kFN + kFN) * 4, "epilogue tiles and conv weights fit the stages");
+  __shared__ __attribute__((aligned(1024))) unsigned short ring[2 * ST];
 
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wr = w >> 1, wc = w & 1;  // row group, channel half
   const int r16 = lane & 15, kq = lane >> 4;
   const int tiles_x = (f.W + kFW - 1) / kFW, tiles_y = (f.Hh + kFH - 1) / kFH;
   const int tiles = f.B * tiles_x * tiles_y;
@@ -115,40 +113,46 @@ __global__ void __launch_bounds__(256) gated_conv_kernel(GatedConvArgs f) {
   const int y0 = ty * kFH, x0 = tx * kFW;
   const int c0 = (j % ncb) * kFN;
   const int64_t L = (int64_t)f.Hh * f.W, K = f.d;
-  const unsigned short* X = static_cast<const unsigned short*>(f.X);
 
-  // conv weights and bias of the work-group's channels (read in the epilogue)
-  if (tid < kFN * 9 / 4) reinterpret_cast<f4*>(wsm)[tid] = reinterpret_cast<const f4*>(f.cw + (int64_t)c0 * 9)[tid];
-  if (tid >= 160 && tid < 160 + kFN / 4) {
-    const int q = tid - 160;
-    reinterpret_cast<f4*>(wsm + kFN * 9)[q] =
-        f.cb ? reinterpret_cast<const f4*>(f.cb + c0)[q] : f4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  // this thread's 16-byte pieces of the A (halo) and B (weight) tiles
-  const w4* ga[kFA];
-  unsigned am[kFA];  // all-ones for a token of the image, zero otherwise
-  int la[kFA];
+  // this lane's global pieces: transfer q of the wave fills halo rows 8 (w + 8 q) ..,
+  // then rows 8 w .. of W_g and of W_v
+  const char* ga[kFA];
+  const char* gb[kFB];
+  const int lr = lane >> 3;
 #pragma unroll
   for (int q = 0; q < kFA; ++q) {
-    const int p = tid + 256 * q, row = p >> 2, col = p & 3;
+    const int row = 8 * (w + kFWaves * q) + lr, col = (lane & 7) ^ kSwz64(row);
     const int hy = row / kFHW, hx = row - hy * kFHW;
-    const int y = y0 - 1 + hy, x = x0 - 1 + hx;
-    const bool in = row < kFV && y >= 0 && y < f.Hh && x >= 0 && x < f.W;
-    ga[q] = reinterpret_cast<const w4*>(X + (in ? (b * L + (int64_t)y * f.W + x) * K : 0) + 8 * col);
-    am[q] = in ? 0xffffffffu : 0u;
-    la[q] = row * kPitch + 8 * (col ^ kSwz(row));
+    const int y = min(max(y0 - 1 + hy, 0), f.Hh - 1), x = min(max(x0 - 1 + hx, 0), f.W - 1);
+    ga[q] = static_cast<const char*>(f.X) + ((b * L + (int64_t)y * f.W + x) * K + 8 * col) * 2;
   }
-  // weight pieces: piece p < 4 kFN of the W_g tile, then the W_v tile
-  const w4* gb[kFB];
-  int lb[kFB];
 #pragma unroll
   for (int q = 0; q < kFB; ++q) {
-    const int p = tid + 256 * q, v = p / (kFN * 4), r = (p % (kFN * 4)) >> 2, col = p & 3;
-    gb[q] = reinterpret_cast<const w4*>(static_cast<const unsigned short*>(v ? f.Wv : f.Wg) + (int64_t)(c0 + r) * K +
-                                        8 * col);
-    lb[q] = SA + v * SB + r * kPitch + 8 * (col ^ kSwz(r));
+    const int row = 8 * w + lr, col = (lane & 7) ^ kSwz64(row);
+    gb[q] = static_cast<const char*>(q ? f.Wv : f.Wg) + ((int64_t)(c0 + row) * K + 8 * col) * 2;
   }
+  const unsigned lbase = lds_addr(ring) + w * 1024;
+  auto issue = [&](int buf) {
+    const unsigned l = lbase + buf * ST * 2;
+#pragma unroll
+    for (int q = 0; q < kFA; ++q) {
+      dma16(ga[q], l + kFWaves * 1024 * q);
+      ga[q] += 128;
+    }
+#pragma unroll
+    for (int q = 0; q < kFB; ++q) {
+      dma16(gb[q], l + (SA + q * SB) * 2);
+      gb[q] += 128;
+    }
+  };
+  issue(0);
+
+  // conv weights and bias of the work-group's channels, for the epilogue
+  f4 cwv = {0.f, 0.f, 0.f, 0.f};
+  if (tid < kFN * 9 / 4)
+    cwv = reinterpret_cast<const f4*>(f.cw + (int64_t)c0 * 9)[tid];
+  else if (tid < kFN * 10 / 4 && f.cb)
+    cwv = reinterpret_cast<const f4*>(f.cb + c0)[tid - kFN * 9 / 4];
 
   f4 av[VT][NJ], ag[GT][NJ];
 #pragma unroll
@@ -160,127 +164,129 @@ __global__ void __launch_bounds__(256) gated_conv_kernel(GatedConvArgs f) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) ag[t][j] = f4{0.f, 0.f, 0.f, 0.f};
 
-  constexpr int D = 4;
-  w4 ra[D][kFA], rb[D][kFB];
-  auto fetch = [&](int s, w4 (&a)[kFA], w4 (&b)[kFB]) {
+  const int steps = f.d / 64;
+  for (int s = 0; s < steps; ++s) {
+    ring_wait<0>();  // this step's stage has landed, every wave is done with the other one
+    if (s + 1 < steps) issue((s & 1) ^ 1);
+    const unsigned short* S = ring + (s & 1) * ST;
 #pragma unroll
-    for (int q = 0; q < kFA; ++q) a[q] = ga[q][4 * s];
+    for (int h = 0; h < 2; ++h) {
+      auto frag = [&](const unsigned short* base, int row) {
+        return OP::get(*reinterpret_cast<const w4*>(&base[row * kPitch64 + 8 * ((4 * h + kq) ^ kSwz64(row))]));
+      };
+      typename OP::T fg[NJ], fv[NJ];
 #pragma unroll
-    for (int q = 0; q < kFB; ++q) b[q] = gb[q][4 * s];
-  };
-  auto stage = [&](int buf, const w4 (&a)[kFA], const w4 (&b)[kFB]) {
-    unsigned short* S = stg[buf];
+      for (int j = 0; j < NJ; ++j) {
+        fv[j] = frag(S + SA + SB, 32 * wc + 16 * j + r16);
+        fg[j] = frag(S + SA, 32 * wc + 16 * j + r16);
+      }
 #pragma unroll
-    for (int q = 0; q < kFA; ++q) *reinterpret_cast<w4*>(&S[la[q]]) = a[q] & am[q];  // zero outside the image
+      for (int t = 0; t < VT; ++t) {
+        const typename OP::T fa = frag(S, 16 * (VT * wr + t) + r16);
 #pragma unroll
-    for (int q = 0; q < kFB; ++q) *reinterpret_cast<w4*>(&S[lb[q]]) = b[q];
-  };
-  auto frag = [&](const unsigned short* S, int row) {
-    return OP::get(*reinterpret_cast<const w4*>(&S[row * kPitch + 8 * (kq ^ kSwz(row))]));
-  };
-  const int steps = f.d / 32;
+        for (int j = 0; j < NJ; ++j) av[t][j] = mfma(fv[j], fa, av[t][j]);  // V^T tiles
+      }
 #pragma unroll
-  for (int q = 0; q < D; ++q)
-    if (q < steps) fetch(q, ra[q], rb[q]);
-  stage(0, ra[0], rb[0]);
-  __syncthreads();
-  for (int sb = 0; sb < steps; sb += D) {
+      for (int t = 0; t < GT; ++t) {
+        const int ci = GT * wr + t;  // tile row: halo rows (ci + 1) * kFHW + 1 .. + 16
+        const typename OP::T fa = frag(S, (ci + 1) * kFHW + 1 + r16);
 #pragma unroll
-    for (int q = 0; q < D; ++q) {
-      const int s = sb + q;
-      if (s < steps) {
-        const unsigned short* S = stg[s & 1];
-        if (s + D < steps) fetch(s + D, ra[q], rb[q]);  // slot q was staged before this step
-        typename OP::T fg[NJ], fv[NJ];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          fg[j] = frag(S + SA, 16 * j + r16);
-          fv[j] = frag(S + SA + SB, 16 * j + r16);
-        }
-#pragma unroll
-        for (int t = 0; t < VT; ++t) {
-          const typename OP::T fa = frag(S, 16 * (VT * w + t) + r16);
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) av[t][j] = mfma(fv[j], fa, av[t][j]);  // V^T tiles
-        }
-#pragma unroll
-        for (int t = 0; t < GT; ++t) {
-          const int ci = GT * w + t;  // tile row: halo rows (ci + 1) * kFHW + 1 .. + 16
-          const typename OP::T fa = frag(S, (ci + 1) * kFHW + 1 + r16);
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) ag[t][j] = mfma(fg[j], fa, ag[t][j]);  // G^T tiles
-        }
-        if (s + 1 < steps) stage((s & 1) ^ 1, ra[(q + 1) % D], rb[(q + 1) % D]);
-        __syncthreads();
+        for (int j = 0; j < NJ; ++j) ag[t][j] = mfma(fg[j], fa, ag[t][j]);  // G^T tiles
       }
     }
   }
 
   // epilogue: V [192 halo rows][kFN] and G [128 tile tokens][kFN] in fp16, in
-  // the stage buffers (every wave passed the K loop's last barrier). The
-  // 16-byte piece p of row r sits at piece p ^ eswz(r): the C^T writes (16
-  // rows x 2 half-pieces per 32 lanes) and the convolution's reads (4
+  // the stages. The 16-byte piece p of row r sits at piece p ^ eswz(r): the C^T
+  // writes (16 rows x 2 half-pieces per 32 lanes) and the convolution's reads (4
   // consecutive rows x 8 pieces per 32 lanes) then both spread over all banks;
   // unswizzled, the writes of rows r, r + 2, r + 4, ... hit the same banks.
-  _Float16* Vt = reinterpret_cast<_Float16*>(&stg[0][0]);
+  ring_sync();  // every wave is past the K loop's last LDS read
+  _Float16* Vt = reinterpret_cast<_Float16*>(ring);
   _Float16* Gt = Vt + kFVT * 16 * kFN;
+  float* wsm = reinterpret_cast<float*>(ring + kTiles);  // [9 taps][kFN], then the bias [kFN]
   auto eswz = [](int row) { return (row >> 1) & (kFP - 1); };
+  if (tid < kFN * 9 / 4) {
 #pragma unroll
-  for (int t = 0; t < VT; ++t)
+    for (int e = 0; e < 4; ++e) {
+      const int i = 4 * tid + e, ch = i / 9;
+      wsm[(i - 9 * ch) * kFN + ch] = cwv[e];
+    }
+  } else if (tid < kFN * 10 / 4) {
+    reinterpret_cast<f4*>(wsm)[tid] = cwv;
+  }
+#pragma unroll
+  for (int t = 0; t < VT; ++t) {
+    const int row = 16 * (VT * wr + t) + r16;
+    const int hy = row / kFHW, hx = row - hy * kFHW;
+    const bool in = (unsigned)(y0 - 1 + hy) < (unsigned)f.Hh && (unsigned)(x0 - 1 + hx) < (unsigned)f.W;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int row = 16 * (VT * w + t) + r16;
-      const h4 hv = {(_Float16)av[t][j][0], (_Float16)av[t][j][1], (_Float16)av[t][j][2], (_Float16)av[t][j][3]};
-      *reinterpret_cast<h4*>(&Vt[row * kFN + 8 * ((2 * j + (kq >> 1)) ^ eswz(row)) + 4 * (kq & 1)]) = hv;
+      h4 hv = {(_Float16)av[t][j][0], (_Float16)av[t][j][1], (_Float16)av[t][j][2], (_Float16)av[t][j][3]};
+      if (!in) hv = h4{0, 0, 0, 0};
+      *reinterpret_cast<h4*>(&Vt[row * kFN + 8 * ((4 * wc + 2 * j + (kq >> 1)) ^ eswz(row)) + 4 * (kq & 1)]) = hv;
     }
+  }
 #pragma unroll
   for (int t = 0; t < GT; ++t)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int row = 16 * (GT * w + t) + r16;
+      const int row = 16 * (GT * wr + t) + r16;
       const h4 hg = {(_Float16)ag[t][j][0], (_Float16)ag[t][j][1], (_Float16)ag[t][j][2], (_Float16)ag[t][j][3]};
-      *reinterpret_cast<h4*>(&Gt[row * kFN + 8 * ((2 * j + (kq >> 1)) ^ eswz(row)) + 4 * (kq & 1)]) = hg;
+      *reinterpret_cast<h4*>(&Gt[row * kFN + 8 * ((4 * wc + 2 * j + (kq >> 1)) ^ eswz(row)) + 4 * (kq & 1)]) = hg;
     }
   __syncthreads();
 
-  // gated convolution: 8 channels (piece pc) of kFH kFW kFP / 256 tile tokens per thread
-  const int pc = tid & (kFP - 1), tg = tid / kFP;
-  float wt[72];  // wt[9 e + 3 u + v]: tap (u, v) of channel 8 pc + e
+  // gated convolution: 8 channels (piece pc) of NR tokens one below the other
+  // per thread, which share the halo rows between them
+  constexpr int NR = kFH * kFW * kFP / NT;  // 2
+  const int pc = tid & (kFP - 1), tg = tid / kFP, cj = tg % kFW, ci = tg / kFW * NR;
+  h8 out[NR];
 #pragma unroll
-  for (int q = 0; q < 18; ++q) {
-    const f4 x = reinterpret_cast<const f4*>(wsm + 72 * pc)[q];
+  for (int hf = 0; hf < 2; ++hf) {  // 4 of the 8 channels at a time: the 9 taps of all 8 take 72 registers
+    float acc[NR][4];
+    const f4 bias = *reinterpret_cast<const f4*>(&wsm[9 * kFN + 8 * pc + 4 * hf]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) wt[4 * q + e] = x[e];
-  }
-  const f4 blo = reinterpret_cast<const f4*>(wsm + kFN * 9 + 8 * pc)[0];
-  const f4 bhi = reinterpret_cast<const f4*>(wsm + kFN * 9 + 8 * pc)[1];
+    for (int m = 0; m < NR; ++m)
 #pragma unroll
-  for (int m = 0; m < kFH * kFW * kFP / 256; ++m) {
-    const int ct = tg + 256 / kFP * m, ci = ct / kFW, cj = ct % kFW;
-    float acc[8];
+      for (int e = 0; e < 4; ++e) acc[m][e] = bias[e];
+    f4 wt[3][3];  // wt[u][v][e]: tap (u, v) of channel 8 pc + 4 hf + e
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[e] = blo[e];
-      acc[e + 4] = bhi[e];
-    }
+    for (int hr = 0; hr < NR + 2; ++hr) {
+      if (hr < 3)
 #pragma unroll
-    for (int u = 0; u < 3; ++u)
+        for (int v = 0; v < 3; ++v) wt[hr][v] = *reinterpret_cast<const f4*>(&wsm[(3 * hr + v) * kFN + 8 * pc + 4 * hf]);
 #pragma unroll
       for (int v = 0; v < 3; ++v) {
-        const int row = (ci + u) * kFHW + cj + v;
-        const h8 x = *reinterpret_cast<const h8*>(&Vt[row * kFN + 8 * (pc ^ eswz(row))]);
+        const int row = (ci + hr) * kFHW + cj + v;
+        const h4 x = *reinterpret_cast<const h4*>(&Vt[row * kFN + 8 * (pc ^ eswz(row)) + 4 * hf]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = fmaf((float)x[e], wt[9 * e + 3 * u + v], acc[e]);
+        for (int m = 0; m < NR; ++m) {
+          const int u = hr - m;  // the tap row of token ci + m that this halo row is under
+          if (u < 0 || u > 2) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[m][e] = fmaf((float)x[e], wt[u][v][e], acc[m][e]);
+        }
       }
-    const h8 g8 = *reinterpret_cast<const h8*>(&Gt[ct * kFN + 8 * (pc ^ eswz(ct))]);
-    h8 out;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float z = (float)g8[e];
-      out[e] = (_Float16)(z * __builtin_amdgcn_rcpf(1.f + __expf(-z)) * acc[e]);
     }
-    const int y = y0 + ci, x = x0 + cj;
-    if (y < f.Hh && x < f.W) *reinterpret_cast<h8*>(f.H + (b * L + (int64_t)y * f.W + x) * f.hidden + c0 + 8 * pc) = out;
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const int ct = (ci + m) * kFW + cj;
+      const h4 g4 = *reinterpret_cast<const h4*>(&Gt[ct * kFN + 8 * (pc ^ eswz(ct)) + 4 * hf]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float z = (float)g4[e];
+        acc[m][e] *= z * __builtin_amdgcn_rcpf(1.f + __expf(-z));
+        // computed here: sunk into the guarded store, the products hold every operand in registers till then
+        asm volatile("" : "+v"(acc[m][e])::"memory");
+        out[m][4 * hf + e] = (_Float16)acc[m][e];
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int y = y0 + ci + m, x = x0 + cj;
+    if (y < f.Hh && x < f.W) *reinterpret_cast<h8*>(f.H + (b * L + (int64_t)y * f.W + x) * f.hidden + c0 + 8 * pc) = out[m];
   }
 }
 
@@ -456,9 +462,9 @@ extern "C" gtr_status gtr_spatial_swiglu(const gtr_swiglu_args* a, hipStream_t s
   const int64_t tiles = (int64_t)a->B * ((a->H + kFH - 1) / kFH) * ((a->W + kFW - 1) / kFW);
   const dim3 grid1((unsigned)(tiles * (a->hidden / kFN)));
   if (bf)
-    hipLaunchKernelGGL(gated_conv_kernel<GTR_BF16>, grid1, dim3(256), 0, stream, gc);
+    hipLaunchKernelGGL(gated_conv_kernel<GTR_BF16>, grid1, dim3(64 * kFWaves), 0, stream, gc);
   else
-    hipLaunchKernelGGL(gated_conv_kernel<GTR_F16>, grid1, dim3(256), 0, stream, gc);
+    hipLaunchKernelGGL(gated_conv_kernel<GTR_F16>, grid1, dim3(64 * kFWaves), 0, stream, gc);
   if (hipGetLastError() != hipSuccess) return GTR_ERR_HIP;
 
   const int ks = out_ksplit(M, a->d, a->hidden);

@@ -566,7 +566,7 @@ def test_swiglu_gated_conv_addresses(dt, B, H, W, d, hidden):
 
     ids = sorted({block_of(t, c) for t in (0, tx - 1, nt - 1, nt // 2) for c in (0, nc - 1)})
     assert all(0 <= b < T for b in ids)
-    check_kernel(text, name, kern, regions, [(b, 0, 0) for b in ids])
+    check_kernel(text, name, kern, regions, [(b, 0, 0) for b in ids], waves=8)
 
 
 @pytest.mark.parametrize("cdt", [0, 1, 2])
