@@ -118,7 +118,12 @@ typedef enum {
                           16 chunks: the last chunk of each group also hands over
                           the group's aggregate, and a chunk sums the summaries
                           of its own group and then one aggregate per earlier
-                          group. At most 1024 sequences of 256 chunks.              */
+                          group. Where the chunks are several times the
+                          work-groups that fit, a work-group takes a segment of
+                          consecutive chunks instead: it hands over the segment's
+                          aggregate, sums the aggregates of the segments before
+                          it and carries the state through its own chunks.
+                          At most 1024 sequences of 256 chunks.                     */
   GTR_PATH_STAGED = 2, /* three launches: summaries, boundary-state scan, outputs;
                           no waits between work-groups                             */
   GTR_PATH_INLINE = 3  /* one launch, each chunk rebuilds its boundary state from

@@ -73,6 +73,7 @@ struct GlaParams {
   int nxcd;     // one launch, 16-bit kernel: XCDs of the sequence-per-XCD grid (0: plain chunk-major grid)
   unsigned spin;  // polls of a bounded wait
   int group;      // one launch, 16-bit kernel: grouped look-back (kGroup chunks per group)
+  int segc;       // segment kernel: chunks per work-group
   unsigned hrec;  // min(floor(2^32 / H), 2^32 - 1): division by H of the column scans
 };
 
@@ -500,6 +501,7 @@ struct LeanKernels {
   const void* split3;
   const void* whole4;
   const void* split4;
+  const void* seg;  // segments of several chunks per work-group (no value split)
 };
 bool lean_kernels(int qdt, int dk, int dv, int chunk, LeanKernels* out);
 

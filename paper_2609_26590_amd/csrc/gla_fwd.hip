@@ -960,6 +960,7 @@ struct KernelSet {
   const void* lean_split;   // the same with d_v split in two, else null
   const void* lean4;        // the same at four work-groups per CU
   const void* lean4_split;
+  const void* seg;          // the 16-bit kernel in segments of several chunks
   // the one-launch kernels that run: the lean ones where they exist (occ4:
   // the four-per-CU instantiation)
   const void* one(bool occ4 = false) const { return lean ? (occ4 ? lean4 : lean) : chain; }
@@ -1011,6 +1012,7 @@ static bool select_kernels(const GlaShape& s, KernelSet* ks) {
     ks->lean_split = lk.split3;
     ks->lean4 = lk.whole4;
     ks->lean4_split = lk.split4;
+    ks->seg = lk.seg;
   }
   return ok;
 }
@@ -1073,6 +1075,7 @@ struct Plan {
   int nxcd;     // sequence-per-XCD grid of the 16-bit kernel (0: chunk-major grid)
   int group;    // grouped look-back (16-bit kernel, FUSED)
   int occ4;     // 16-bit kernel at four work-groups per CU
+  int segc;     // chunks per work-group of the segment kernel (0: one work-group per chunk)
   int64_t blocks;
 };
 
@@ -1090,6 +1093,8 @@ struct Plan {
 //   * the value split (d_v = 64 in two halves, no output gate: its RMSNorm needs
 //     whole rows) when the doubled grid still gives every work-group a CU of
 //     its own;
+//   * where the grid is several rounds of work-groups, FUSED on the 16-bit
+//     kernel runs segments of several chunks per work-group (gla_seg_kernel);
 //   * the chunk-major grid, in descending chunk order when every work-group is
 //     resident at once (ascending for the grouped look-back).
 // An explicit path that does not fit is GTR_ERR_UNSUPPORTED; STAGED always fits.
@@ -1100,6 +1105,8 @@ constexpr int64_t kFusedMaxChunks = 64;  // longer sequences: the staged kernels
 // kPublishEvery chunks)
 constexpr int64_t kGroupMinChunks = kInlineMaxChunks + 1;
 
+constexpr int64_t kSegMax = 64;  // segments per sequence: one ballot of their flags
+
 static gtr_status plan_call(const GlaShape& s, int path, bool gate, const KernelSet& ks, Plan* pl) {
   pl->sched = GTR_PATH_STAGED;
   pl->vparts = 1;
@@ -1107,6 +1114,7 @@ static gtr_status plan_call(const GlaShape& s, int path, bool gate, const Kernel
   pl->nxcd = 0;
   pl->group = 0;
   pl->occ4 = 0;
+  pl->segc = 0;
   pl->blocks = 0;
   if (path == GTR_PATH_STAGED) return GTR_OK;
   const bool fits = s.nchunks <= kMaxChainChunks && s.BH <= kSyncSeqs;
@@ -1156,6 +1164,27 @@ static gtr_status plan_call(const GlaShape& s, int path, bool gate, const Kernel
   // wait longest start first), except for the grouped look-back, whose
   // aggregates come from the low chunks
   pl->desc = all_resident && !pl->group ? 1 : 0;
+  // segments where the chunks are several times the work-groups that fit: 6 per
+  // CU for sequences longer than kInlineMaxChunks, 8 (d_k 64) or 12 per CU for
+  // shorter ones, whose look-backs are short. Measured (us, one work-group per
+  // chunk against segments): d_k 64, 100 to 256 chunks per sequence: 1200 chunks
+  // 44.4 / 44.7, 1320 45.4 / 47.2, 1536 60.2 / 55.1, 2048 93 / 62, 4608 137 / 97; 25
+  // chunks: 1800 37.8 / 39.1, 2100 46.5 / 41.1, 2400 54.8 / 50.0, 4800 98.5 / 84.2.
+  // d_k 32, d_v 64: 1320 34.1 / 34.1, 1536 45.2 / 39.7, 2048 69.6 / 41.7, 4608 88 / 63;
+  // 25 chunks: 2400 30.7 / 35.1, 4800 60.2 / 56.3. d_k 32, d_v 32: 1536 39.9 / 33.7,
+  // 4608 69.8 / 49.1; 25 chunks: 2400 25.1 / 25.0, 4800 43.6 / 39.1.
+  const int64_t per = s.nchunks > kInlineMaxChunks ? 6 : (s.dk == 64 ? 8 : 12);
+  if (pl->sched == GTR_PATH_FUSED && pl->vparts == 1 && ks.seg && cus > 0 && ns * s.nchunks >= per * cus) {
+    int c2 = 0;
+    const int64_t slots = (int64_t)resident_per_cu(ks.seg, ks.threads, &c2) * c2;
+    const int64_t nmax = slots / ns < kSegMax ? slots / ns : kSegMax;  // segments per sequence, all resident
+    if (nmax > 1) {
+      pl->segc = (int)((s.nchunks + nmax - 1) / nmax);
+      pl->nxcd = pl->group = pl->desc = 0;
+      pl->blocks = ns * ((s.nchunks + pl->segc - 1) / pl->segc);
+      return GTR_OK;
+    }
+  }
   pl->blocks = pl->nxcd > 1 ? (int64_t)pl->nxcd * ((ns + pl->nxcd - 1) / pl->nxcd) * s.nchunks : ns * s.nchunks;
   return GTR_OK;
 }
@@ -1254,12 +1283,13 @@ static gtr_status gla_launch(const gtr_gla_args* a, const GlaShape& s, hipStream
   P.nxcd = pl.nxcd;
   P.spin = a->spin_limit ? a->spin_limit : kSpinDefault;
   P.group = pl.group;
+  P.segc = pl.segc;
   P.hrec = a->H > 1 ? (unsigned)(((uint64_t)1 << 32) / (unsigned)a->H) : 0xffffffffu;
 
   void* kargs[] = {&P};
   hipError_t err;
   if (pl.sched != GTR_PATH_STAGED) {
-    const void* k = pl.vparts > 1 ? ks.one_split(pl.occ4) : ks.one(pl.occ4);
+    const void* k = pl.segc ? ks.seg : pl.vparts > 1 ? ks.one_split(pl.occ4) : ks.one(pl.occ4);
     err = hipLaunchKernel(k, dim3((unsigned)pl.blocks), dim3(ks.threads), kargs, 0, stream);
   } else {
     err = hipLaunchKernel(ks.summary, dim3((unsigned)s.nchunks, (unsigned)s.BH), dim3(ks.threads), kargs, 0, stream);

@@ -94,8 +94,8 @@ struct Lean {
   float qh[KS][8];   // q 2^(a_r)
   float ke[KS][8];   // k 2^(T_R - a_r)
   h8 qt[KS];         // q 2^(A_r), the readout operand
-  float spanmax;     // wave-uniform: widest log2-decay across the sub-chunk
-  float absmax;      // wave-uniform: largest |q|, |k| of the sub-chunk
+  bool diag16;       // wave-uniform: the diagonal block's factors and operands fit fp16
+  bool diag32;       // wave-uniform: its factors fit float32
   float usc;         // chunk-uniform: U_c travels as fp16(U_c / usc)
   float pup;         // wave-uniform: the fp16 score tile holds P / pup
   float tsc;         // chunk-uniform: the fp16 state tile holds S_[c] / tsc
@@ -108,7 +108,7 @@ struct Lean {
   __device__ __forceinline__ static uint32_t piece_elem(int m) { return (uint32_t)(piece_i(m) * DV + piece_n0(m)); }
 
   __device__ __forceinline__ void lanes() {
-    w = threadIdx.x >> 6;
+    w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar branches and addresses
     lane = threadIdx.x & 63;
     tr = lane & 15;
     g = lane >> 4;
@@ -120,20 +120,30 @@ struct Lean {
     return valid ? scan_token(P, pos) : 0u;
   }
 
+  // The lane's place as values the compiler does not know: inside a loop over
+  // chunks it then forms the LDS addresses anew per chunk (a few instructions)
+  // instead of keeping all of them in registers.
+  __device__ __forceinline__ void forget_lanes() { asm volatile("" : "+v"(tr), "+v"(g), "+v"(r), "+v"(lane)); }
+
   // LDS address for the transposing read that gives lane (g, i) the column
   // c0 + i of rows r0 + 0..3 of a row-major tile with pitch `pitch`.
   __device__ __forceinline__ const _Float16* tr_addr(const _Float16* tile, int pitch, int r0, int c0) const {
     return tile + (r0 + (tr >> 2)) * pitch + c0 + 4 * (tr & 3);
   }
 
-  // Loads and per-token work; ends with the barrier after which every wave's
-  // key and value rows, sub-chunk totals and maxima are in shared memory.
-  template <class S>
-  __device__ __forceinline__ void load(const GlaParams& P, S& sm, int bh, int c) {
-    lanes();
-    tok = token(P, (unsigned)(c * C) + r, tok_ok);
-    const unsigned t = tok;
-    const bool valid = tok_ok;
+  // The raw rows of this lane's token (position past the end: zeros).
+  struct Rows {
+    Raw q[KS], k[KS], g[KS], v[VS];
+    unsigned tok;
+    bool ok;
+  };
+
+  // Issues the loads of chunk c's rows (WITHQ: q as well).
+  template <bool WITHQ>
+  __device__ __forceinline__ void fetch(const GlaParams& P, int bh, int c, Rows& x) {
+    x.tok = token(P, (unsigned)(c * C) + r, x.ok);
+    const unsigned t = x.tok;
+    const bool valid = x.ok;
     const uint32_t gs = P.gdt == GTR_F32 ? 4 : 2;
     const int64_t L = P.L;
     const char* qb = static_cast<const char*>(P.q) + (int64_t)bh * L * DK * 2;
@@ -144,24 +154,43 @@ struct Lean {
     const __amdgpu_buffer_rsrc_t kr = make_rsrc(kb, (uint32_t)(L * DK * 2));
     const __amdgpu_buffer_rsrc_t vr = make_rsrc(vb, (uint32_t)(L * P.dvp * 2));
     const __amdgpu_buffer_rsrc_t gr = make_rsrc(gb, (uint32_t)(L * DK * gs));
-    Raw rq[KS], rk[KS], rg[KS], rv[VS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(gr, P.gdt, valid ? (t * DK + 32 * s + 8 * g) * gs : kOutOfRange, rg[s]);
+    for (int s = 0; s < KS; ++s) ld_raw_buf(gr, P.gdt, valid ? (t * DK + 32 * s + 8 * g) * gs : kOutOfRange, x.g[s]);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(kr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rk[s]);
+    for (int s = 0; s < KS; ++s) ld_raw_buf(kr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, x.k[s]);
 #pragma unroll
     for (int s = 0; s < VS; ++s)
-      ld_raw_buf(vr, IN, valid ? (t * P.dvp + 32 * s + 8 * g) * 2 : kOutOfRange, rv[s]);
+      ld_raw_buf(vr, IN, valid ? (t * P.dvp + 32 * s + 8 * g) * 2 : kOutOfRange, x.v[s]);
+    if constexpr (WITHQ) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) ld_raw_buf(qr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, rq[s]);
+      for (int s = 0; s < KS; ++s) ld_raw_buf(qr, IN, valid ? (t * DK + 32 * s + 8 * g) * 2 : kOutOfRange, x.q[s]);
+    }
+  }
 
+  // Loads and per-token work; ends with the barrier after which every wave's
+  // key and value rows, sub-chunk totals and maxima are in shared memory.
+  template <class S>
+  __device__ __forceinline__ void load(const GlaParams& P, S& sm, int bh, int c) {
+    lanes();
+    Rows x;
+    fetch<true>(P, bh, c, x);
+    tokens<true, true>(P, sm, x);
+  }
+
+  // Per-token work on the rows of x. SCALES: also usc, the scale of a summary
+  // that is handed over.
+  template <bool WITHQ, bool SCALES, class S>
+  __device__ __forceinline__ void tokens(const GlaParams& P, S& sm, const Rows& x) {
+    tok = x.tok;
+    tok_ok = x.ok;
+    const bool valid = tok_ok;
     // log2-decays and their inclusive sums within the sub-chunk
     float a[KS][8], tot[KS][8];
     float spn = 0.f, am = 0.f, vm = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       float gx[8];
-      cvt_raw(rg[s], P.gdt, gx);
+      cvt_raw(x.g[s], P.gdt, gx);
       if (P.gkind == GTR_GATE_LOGITS) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) gx[e] = log_decay(P, gx[e], valid ? P.inv_tau : 0.f);
@@ -177,14 +206,17 @@ struct Lean {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       float kx[8], qx[8];
-      cvt_raw(rk[s], IN, kx);
-      cvt_raw(rq[s], IN, qx);
+      cvt_raw(x.k[s], IN, kx);
+      if constexpr (WITHQ) cvt_raw(x.q[s], IN, qx);
       h8 kh;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        am = fmaxf(am, fmaxf(fabsf(kx[e]), fabsf(qx[e])));
+        if constexpr (WITHQ)
+          am = fmaxf(am, fmaxf(fabsf(kx[e]), fabsf(qx[e])));
+        else
+          am = fmaxf(am, fabsf(kx[e]));
         ke[s][e] = kx[e] * fexp2(tot[s][e] - a[s][e]);
-        qh[s][e] = qx[e] * fexp2(a[s][e]);
+        if constexpr (WITHQ) qh[s][e] = qx[e] * fexp2(a[s][e]);
         kh[e] = (_Float16)ke[s][e];
       }
       *reinterpret_cast<h8*>(&sm.ke[r * RP + 32 * s + 8 * g]) = kh;
@@ -198,12 +230,12 @@ struct Lean {
     for (int s = 0; s < VS; ++s) {
       h8 vh;
       if constexpr (IN == GTR_F16) {
-        vh = __builtin_bit_cast(h8, rv[s].a);
+        vh = __builtin_bit_cast(h8, x.v[s].a);
 #pragma unroll
         for (int e = 0; e < 8; ++e) vm = fmaxf(vm, fabsf((float)vh[e]));
       } else {
         float vx[8];
-        cvt_raw(rv[s], IN, vx);
+        cvt_raw(x.v[s], IN, vx);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           vm = fmaxf(vm, fabsf(vx[e]));
@@ -212,29 +244,45 @@ struct Lean {
       }
       *reinterpret_cast<h8*>(&sm.v[r * VP + 32 * s + 8 * g]) = vh;
     }
-    spanmax = wave_max_uniform(spn);
-    absmax = wave_max_uniform(am);
-    vm = wave_max_uniform(vm);
-    if (lane == 0) {
-      sm.M[w][0] = absmax;
-      sm.M[w][1] = vm;
+    if constexpr (WITHQ) {
+      constexpr float kSpanF16b = kSpanF16 * kLog2e, kSpanF32b = kSpanF32 * kLog2e;
+      diag16 = __builtin_amdgcn_ballot_w64(!(spn <= kSpanF16b && am <= 256.f)) == 0;
+      diag32 = __builtin_amdgcn_ballot_w64(!(spn <= kSpanF32b)) == 0;
     }
-    __syncthreads();
-    float amx = 0.f, vmx = 0.f;
+    range_bad = false;
+    if constexpr (SCALES) {
+      am = wave_max_uniform(am);
+      vm = wave_max_uniform(vm);
+      if (lane == 0) {
+        sm.M[w][0] = am;
+        sm.M[w][1] = vm;
+      }
+      __syncthreads();
+      float amx = 0.f, vmx = 0.f;
 #pragma unroll
-    for (int K = 0; K < NW; ++K) {
-      amx = fmaxf(amx, sm.M[K][0]);
-      vmx = fmaxf(vmx, sm.M[K][1]);
+      for (int K = 0; K < NW; ++K) {
+        amx = fmaxf(amx, sm.M[K][0]);
+        vmx = fmaxf(vmx, sm.M[K][1]);
+      }
+      // |U_c| <= C max|k| max|v|; NaN maxima (non-finite inputs) count as out of range
+      range_bad = IN == GTR_BF16 && !(amx <= kF16Safe && vmx <= kF16Safe);
+      usc = exp2i(fp16_exponent((float)C * amx * vmx));
+    } else {
+      if constexpr (IN == GTR_BF16) {
+        const bool bad = __builtin_amdgcn_ballot_w64(!(am <= kF16Safe && vm <= kF16Safe)) != 0;
+        if (lane == 0) sm.M[w][0] = bad ? 1.f : 0.f;
+      }
+      __syncthreads();
+      if constexpr (IN == GTR_BF16)
+        range_bad = sm.M[0][0] + sm.M[1][0] + sm.M[2][0] + sm.M[3][0] > 0.f;
     }
-    // |U_c| <= C max|k| max|v|; NaN maxima (non-finite inputs) count as out of range
-    range_bad = IN == GTR_BF16 && !(amx <= kF16Safe && vmx <= kF16Safe);
-    usc = exp2i(fp16_exponent((float)C * amx * vmx));
   }
 
   // Factors per key dim (lane d of each wave for its sub-chunk), d_c, and the
   // readout operand; ends with the barrier after which every wave's factors
   // are visible (the summary scales each sub-chunk's keys by its own).
-  template <class S>
+  // WITHQ false: only the summary's (k-hat factors, d_c).
+  template <bool WITHQ = true, class S>
   __device__ __forceinline__ void factors(S& sm) {
     if (lane < DK) {
       const int d = lane;
@@ -247,13 +295,13 @@ struct Lean {
         after += K > w ? tK[K] : 0.f;
         all += tK[K];
       }
-      sm.F[w][kFq][d] = fexp2(before);
       sm.F[w][kFk][d] = fexp2(after);
-      sm.F[w][kFh][d] = fexp2(-0.5f * tK[w]);
+      if constexpr (WITHQ) sm.F[w][kFq][d] = fexp2(before);
+      if constexpr (WITHQ) sm.F[w][kFh][d] = fexp2(-0.5f * tK[w]);
       float acc = 0.f;  // sum of the totals strictly between J and w, J = w-1, w-2, ...
 #pragma unroll
       for (int J = NW - 2; J >= 0; --J) {
-        if (J < w) {
+        if (WITHQ && J < w) {
           sm.F[w][kFoff + J][d] = fexp2(acc);
           acc += tK[J];
         }
@@ -261,6 +309,7 @@ struct Lean {
       if (w == 0) sm.dc[d] = fexp2(all);
     }
     __syncthreads();
+    if constexpr (!WITHQ) return;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const f4 lo = *reinterpret_cast<const f4*>(&sm.F[w][kFq][32 * s + 8 * g]);
@@ -283,19 +332,7 @@ struct Lean {
     f4 acc[NTILE];
 #pragma unroll
     for (int m = 0; m < NTILE; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks) {
-      const int t0 = 32 * ks + 8 * g;  // this lane's tokens t0 .. t0 + 7
-      const h8 A = cat(ld_tr(tr_addr(sm.v, VP, t0, 16 * jb)), ld_tr(tr_addr(sm.v, VP, t0 + 4, 16 * jb)));
-      const int Rk = t0 / 16;
-#pragma unroll
-      for (int m = 0; m < NTILE; ++m) {
-        const int ib = (w + NW * m) / VB;
-        const h8 Bk = cat(ld_tr(tr_addr(sm.ke, RP, t0, 16 * ib)), ld_tr(tr_addr(sm.ke, RP, t0 + 4, 16 * ib)));
-        const _Float16 f = (_Float16)sm.F[Rk][kFk][16 * ib + tr];
-        acc[m] = mma32(A, Bk * f, acc[m]);
-      }
-    }
+    add_summary(sm, acc);
     // lane (g, i): acc[m][e] = U[16 ib + i][16 jb + 4 g + e]
     const float down = range_bad ? __builtin_nanf("") : 1.f / usc;
     const __amdgpu_buffer_rsrc_t ur = make_rsrc(U, DK * DV * 2);
@@ -309,6 +346,26 @@ struct Lean {
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, hv), ur, off, 0, 0);
       else
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, hv), ur, off, 0, kAgentCoherent);
+    }
+  }
+
+  // acc += U_c, this wave's tiles: lane (g, i) holds acc[m][e] = [16 ib + i][16 jb
+  // + 4 g + e] with jb = w % VB, ib = (w + NW m) / VB.
+  template <class S>
+  __device__ __forceinline__ void add_summary(const S& sm, f4 (&acc)[NTILE]) const {
+    const int jb = w % VB;
+#pragma unroll
+    for (int ks = 0; ks < C / 32; ++ks) {
+      const int t0 = 32 * ks + 8 * g;  // this lane's tokens t0 .. t0 + 7
+      const h8 A = cat(ld_tr(tr_addr(sm.v, VP, t0, 16 * jb)), ld_tr(tr_addr(sm.v, VP, t0 + 4, 16 * jb)));
+      const int Rk = t0 / 16;
+#pragma unroll
+      for (int m = 0; m < NTILE; ++m) {
+        const int ib = (w + NW * m) / VB;
+        const h8 Bk = cat(ld_tr(tr_addr(sm.ke, RP, t0, 16 * ib)), ld_tr(tr_addr(sm.ke, RP, t0 + 4, 16 * ib)));
+        const _Float16 f = (_Float16)sm.F[Rk][kFk][16 * ib + tr];
+        acc[m] = mma32(A, Bk * f, acc[m]);
+      }
     }
   }
 
@@ -391,8 +448,7 @@ struct Lean {
     // stay well inside the fp16 range, float32 operands up to e^30, else exact
     {
       f4 D = {0.f, 0.f, 0.f, 0.f};
-      constexpr float kSpanF16b = kSpanF16 * kLog2e, kSpanF32b = kSpanF32 * kLog2e;
-      if (spanmax <= kSpanF16b && absmax <= 256.f) {
+      if (diag16) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const f4 lo = *reinterpret_cast<const f4*>(&sm.F[w][kFh][32 * s + 8 * g]);
@@ -407,7 +463,7 @@ struct Lean {
           }
           D = mma32(a, b, D);
         }
-      } else if (spanmax <= kSpanF32b) {
+      } else if (diag32) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const f4 lo = *reinterpret_cast<const f4*>(&sm.F[w][kFh][32 * s + 8 * g]);
@@ -818,10 +874,287 @@ gla_lean_kernel(GlaParams P) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Segments: the one-launch schedule where the grid is more than one round of
+// work-groups (many sequences, or long ones). A work-group owns P.segc
+// consecutive chunks of one sequence, chosen so that every work-group of the
+// grid is resident at once, and goes through them twice:
+//   1. forward over k, v, g: the segment's aggregate A = sum_j (prod_{l>j}
+//      Diag(d_l)) U_j and D = prod_j d_j, in float32 in the MFMA accumulators;
+//      A (fp16, a power-of-two scale per row) and the record (D, scale) are
+//      handed over and the segment's flag goes up (the last segment skips this);
+//   2. the state before the segment from the aggregates of the segments before
+//      it (at most 63, nearest first, decay products between them) and S_0;
+//   3. forward over q, k, v, g: outputs, the state carried from chunk to chunk
+//      in float32 in the accumulators: no hand-off between its own chunks.
+// Reading k, v and g twice costs less than what it replaces: with one work-group
+// per chunk every chunk wrote its summary, waited for those before it and read
+// up to 22 of them back, round after round of work-groups.
+// What bounds it: vector instructions (about two thirds of the cycles at d_k 32;
+// the second pass over k, v, g is about a quarter of them) where the kernel with
+// one work-group per chunk spent two thirds of its cycles waiting. Measured (us,
+// one work-group per chunk -> segments): 128 x 128 tokens, d_k 32, 4 images of 6
+// heads 139 -> 84; 40 x 40, d_k 64, 8 images of 12 heads with states 62.8 -> 57.5;
+// the range in the dispatch rule of gla_fwd.hip.
+// ---------------------------------------------------------------------------
+template <class L>
+struct SegSmem {
+  static constexpr int DK = L::kDK, DV = L::kDV, C = L::NW * 16;
+  union alignas(16) {
+    struct {
+      _Float16 ke[C * L::RP];  // k 2^(T_R - a), token-major
+      _Float16 v[C * L::VP];   // v (fp16), token-major
+    };
+    float sf[DK * (DV + 4)];   // the segment's first state, row-major
+  };
+  alignas(16) _Float16 st[DK * L::SPp];  // S_[c] / tsc, key-dim-major
+  float T[L::NW][DK];
+  float F[L::NW][L::NF][DK];
+  float Pt[L::NW][16][17];
+  float M[L::NW][2];
+  float smax[L::NW];
+  float dc[DK];
+  int okw[L::NW];
+};
+
+// acc = sum over the n segments before segment n (nearest first) of their
+// aggregates, `run` the decay product of all of them.
+template <class T>
+__device__ __forceinline__ void sum_segments(const GlaParams& P, int seq, int n, float (&acc)[T::SPER][8], float& run) {
+  constexpr int SPER = T::SPER;
+  constexpr int B = (T::kDK == 64 ? 40 : 80) / (SPER * 4 + 2);  // tiles per batch, by their registers
+  constexpr uint32_t slot = T::kDK * T::kDV * 4;  // bytes; the aggregate is fp16, its record sits behind it
+  const __amdgpu_buffer_rsrc_t ar = make_rsrc(P.states + (size_t)seq * P.nchunks * (slot / 4), (uint32_t)P.nchunks * slot);
+  const bool mine = T::piece_ok(0);
+  const uint32_t row = (uint32_t)T::piece_i(0);
+#pragma unroll 1
+  for (int k1 = 0; k1 < n; k1 += B) {
+    Piece<true> u[B][SPER];
+    f2 r[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const bool in = k1 + b < n && mine;  // past the end: an offset past the range reads zeros
+      const uint32_t s = (uint32_t)(n - 1 - k1 - b) * slot;
+      r[b] = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(ar, in ? s + slot / 2 + row * 8 : kOutOfRange, 0,
+                                                                         kAgentCoherent));
+#pragma unroll
+      for (int mm = 0; mm < SPER; ++mm) u[b][mm].load(ar, in ? s / 2 + T::piece_elem(mm) : kOutOfRange / 2);
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const float wt = run * r[b][1];  // 0 for a tile read as zeros
+#pragma unroll
+      for (int mm = 0; mm < SPER; ++mm) u[b][mm].fma_into(acc[mm], wt);
+      run = k1 + b < n ? run * r[b][0] : run;
+    }
+  }
+}
+
+template <int DK, int DV, int IN>
+__global__ void __launch_bounds__(tile_threads(64)) __attribute__((amdgpu_waves_per_eu(3)))
+gla_seg_kernel(GlaParams P) {
+  typedef Lean<DK, DV, 64, IN, 3> T;
+  constexpr int NT = T::NTILE;
+  // the next chunk's rows loaded while this one is worked on: in the third part
+  // only where the registers allow it (d_k 32, d_v 64: op at 128 x 128 tokens, 4
+  // images 90 -> 84 us; at d_k 64 it spills, 8 images of 12 heads 57 -> 88 us)
+  constexpr bool PF = DK == 32 && DV == 64;
+  __shared__ SegSmem<T> sm;
+  const int NC = P.nchunks, nseg = (NC + P.segc - 1) / P.segc;
+  // segment-major in ascending order: every work-group waits only on blocks
+  // with smaller indices
+  const int sg = blockIdx.x / P.ns, seq = blockIdx.x - sg * P.ns, bh = seq;
+  const int c0 = sg * P.segc, c1 = min(c0 + P.segc, NC);
+  const bool last = sg == nseg - 1;
+  unsigned* fl = P.flags + (size_t)seq * kMaxChainChunks;
+
+  T ch;
+  ch.lanes();
+  const int jb = ch.w % T::VB;
+  auto row_of = [&](int m) { return 16 * ((ch.w + T::NW * m) / T::VB) + ch.tr; };
+  typename T::Rows x;
+  bool bad_in = false;
+
+  if (!last) {
+    f4 A[NT];
+    float D[NT];
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      A[m] = f4{0.f, 0.f, 0.f, 0.f};
+      D[m] = 1.f;
+    }
+    ch.template fetch<false>(P, bh, c0, x);
+#pragma unroll 1
+    for (int c = c0; c < c1; ++c) {
+      ch.forget_lanes();
+      ch.template tokens<false, false>(P, sm, x);
+      if (c + 1 < c1) ch.template fetch<false>(P, bh, c + 1, x);
+      ch.template factors<false>(sm);
+      bad_in = bad_in || ch.range_bad;
+#pragma unroll
+      for (int m = 0; m < NT; ++m) {
+        const float d = sm.dc[row_of(m)];
+        A[m] *= d;
+        D[m] *= d;
+      }
+      ch.add_summary(sm, A);
+      __syncthreads();  // the tiles are free for the next chunk
+    }
+    // hand over the aggregate: the largest |A| of each row over the value
+    // blocks gives the row's scale
+    float (*rmax)[DK] = reinterpret_cast<float(*)[DK]>(&sm.F[0][0][0]);
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      if (bad_in) A[m] = f4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+      float mx = fmaxf(fmaxf(fabsf(A[m][0]), fabsf(A[m][1])), fmaxf(fabsf(A[m][2]), fabsf(A[m][3])));
+      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      if (ch.g == 0) rmax[jb][row_of(m)] = mx;
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t sr = make_rsrc(P.states + ((size_t)seq * NC + sg) * (DK * DV), DK * DV * 4);
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      const int row = row_of(m);
+      float mx = 0.f;
+#pragma unroll
+      for (int b = 0; b < T::VB; ++b) mx = fmaxf(mx, rmax[b][row]);
+      const int ex = fp16_exponent(mx);
+      const float down = exp2i(-ex);
+      const h4 hv = {(_Float16)(A[m][0] * down), (_Float16)(A[m][1] * down), (_Float16)(A[m][2] * down),
+                     (_Float16)(A[m][3] * down)};
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, hv), sr, (row * DV + 16 * jb + 4 * ch.g) * 2, 0,
+                                            kAgentCoherent);
+      if (jb == 0 && ch.g == 0)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f2{D[m], exp2i(ex)}), sr, DK * DV * 2 + row * 8, 0,
+                                              kAgentCoherent);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_or(&fl[sg], kFlagSummary, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (PF) ch.template fetch<true>(P, bh, c0, x);  // in flight during the look-back
+
+  // the state before the segment
+  bool okw = true;
+  if (sg > 0) {
+    const uint64_t need = sg >= 64 ? ~0ull : (1ull << sg) - 1ull;
+    for (unsigned cnt = 0;;) {
+      const unsigned f =
+          ch.lane < sg ? __hip_atomic_load(&fl[ch.lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      if ((__builtin_amdgcn_ballot_w64((f & kFlagSummary) != 0) & need) == need) break;
+      if (++cnt >= P.spin) {
+        okw = false;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  float acc[T::SPER][8];
+#pragma unroll
+  for (int m = 0; m < T::SPER; ++m)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[m][e] = 0.f;
+  float run = 1.f;
+  if (okw) sum_segments<T>(P, seq, sg, acc, run);
+  add_base<T>(P, seq, -1, run, acc);
+  // one exchange makes the outcome uniform: a wait that ran out, or a NaN
+  // handed over, poisons everything this segment writes
+  bool nan_in = false;
+#pragma unroll
+  for (int m = 0; m < T::SPER; ++m)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) nan_in = nan_in || acc[m][e] != acc[m][e];
+  const bool wave_nan = __builtin_amdgcn_ballot_w64(nan_in) != 0;
+  if (ch.lane == 0) sm.okw[ch.w] = (okw ? 0 : 1) | (wave_nan ? 2 : 0);
+#pragma unroll
+  for (int m = 0; m < T::SPER; ++m)
+    if (T::piece_ok(m)) {
+      f4* dst = reinterpret_cast<f4*>(&sm.sf[T::piece_i(m) * (DV + 4) + T::piece_n0(m)]);
+      dst[0] = f4{acc[m][0], acc[m][1], acc[m][2], acc[m][3]};
+      dst[1] = f4{acc[m][4], acc[m][5], acc[m][6], acc[m][7]};
+    }
+  __syncthreads();
+  int bad = 0;
+#pragma unroll
+  for (int K = 0; K < T::NW; ++K) bad |= sm.okw[K];
+  bool poison = bad != 0;
+  f4 S[NT];
+#pragma unroll
+  for (int m = 0; m < NT; ++m) S[m] = *reinterpret_cast<const f4*>(&sm.sf[row_of(m) * (DV + 4) + 16 * jb + 4 * ch.g]);
+  __syncthreads();
+  unsigned fault = bad & 1 ? kFaultWait : 0u;
+
+#pragma unroll 1
+  for (int c = c0; c < c1; ++c) {
+    const bool have = c > 0 || P.s0;
+    ch.forget_lanes();
+    float mx = 0.f;
+#pragma unroll
+    for (int m = 0; m < NT; ++m)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(S[m][e]));
+    mx = wave_max_uniform(mx);
+    if (ch.lane == 0) sm.smax[ch.w] = mx;
+    if (!PF) ch.template fetch<true>(P, bh, c, x);
+    ch.template tokens<true, false>(P, sm, x);  // ends with a barrier
+    if (ch.range_bad) {
+      poison = true;
+      fault |= kFaultRange;
+    }
+    if (have) {  // the fp16 state tile; its readers of the last chunk are past this chunk's barrier
+      mx = 0.f;
+#pragma unroll
+      for (int K = 0; K < T::NW; ++K) mx = fmaxf(mx, sm.smax[K]);
+      const int ex = fp16_exponent(mx);
+      ch.tsc = exp2i(ex);
+      const float down = exp2i(-ex);
+#pragma unroll
+      for (int m = 0; m < NT; ++m)
+        *reinterpret_cast<h4*>(&sm.st[row_of(m) * T::SPp + 16 * jb + 4 * ch.g]) =
+            h4{(_Float16)(S[m][0] * down), (_Float16)(S[m][1] * down), (_Float16)(S[m][2] * down),
+               (_Float16)(S[m][3] * down)};
+    }
+    ch.factors(sm);  // its barrier also completes the state tile
+    if (PF && c + 1 < c1) ch.template fetch<true>(P, bh, c + 1, x);
+    Raw rz[T::VB];
+    if (P.gate) ch.prefetch_gate(P, bh, rz);
+    f4 O[T::VB];
+    ch.intra(P, sm, bh, c, O);
+#pragma unroll
+    for (int b = 0; b < T::VB; ++b) O[b] *= ch.pup;
+    if (have) ch.readout(sm, O);
+    ch.store(P, bh, c, O, rz, poison);
+    if (c + 1 < c1 || (last && P.s_final)) {
+#pragma unroll
+      for (int m = 0; m < NT; ++m) S[m] *= sm.dc[row_of(m)];
+      ch.add_summary(sm, S);
+    }
+    __syncthreads();  // the tiles are free for the next chunk
+  }
+  if (last && P.s_final) {
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      if (poison) S[m] = f4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+      *reinterpret_cast<f4*>(P.s_final + ((size_t)bh * DK + row_of(m)) * DV + 16 * jb + 4 * ch.g) = S[m];
+    }
+  }
+  if (threadIdx.x == 0) {
+    if (fault) __hip_atomic_fetch_or(P.fault, fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned* done = P.sync + 4 * seq;
+    const unsigned prev = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (prev == (unsigned)nseg - 1) {  // last one out: leave the flags and the count zeroed
+      for (int j = 0; j < nseg; ++j) __hip_atomic_store(&fl[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
 template <int DK, int DV, int IN>
 static void lean_set(LeanKernels* o) {
   o->whole3 = reinterpret_cast<const void*>(&gla_lean_kernel<DK, DV, 64, IN, 3>);
   o->whole4 = reinterpret_cast<const void*>(&gla_lean_kernel<DK, DV, 64, IN, 4>);
+  o->seg = reinterpret_cast<const void*>(&gla_seg_kernel<DK, DV, IN>);
   if constexpr (DV == 64) {
     o->split3 = reinterpret_cast<const void*>(&gla_lean_kernel<DK, 32, 64, IN, 3>);
     o->split4 = reinterpret_cast<const void*>(&gla_lean_kernel<DK, 32, 64, IN, 4>);
@@ -837,7 +1170,7 @@ static bool lean_dims(int dk, int dv, LeanKernels* o) {
 }
 
 bool lean_kernels(int qdt, int dk, int dv, int chunk, LeanKernels* o) {
-  *o = LeanKernels{nullptr, nullptr, nullptr, nullptr};
+  *o = LeanKernels{nullptr, nullptr, nullptr, nullptr, nullptr};
   if (chunk != 64) return false;
   if (qdt == GTR_F16) return lean_dims<GTR_F16>(dk, dv, o);
   if (qdt == GTR_BF16) return lean_dims<GTR_BF16>(dk, dv, o);

@@ -175,9 +175,10 @@ struct Op<false> {
 // ---------------------------------------------------------------------------
 template <int SHIFT>
 __device__ __forceinline__ float row_shr(float x) {
-  // lanes whose source is outside the row receive 0
+  // lanes whose source is outside the row receive 0 (bound_ctrl: the addition
+  // that uses it takes the shift as its own operand, with no move before it)
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
-                                                               0x110 + SHIFT, 0xf, 0xf, false));
+                                                               0x110 + SHIFT, 0xf, 0xf, true));
 }
 
 // Inclusive prefix sum over the 16 lanes of each row.
@@ -196,26 +197,27 @@ __device__ __forceinline__ float row_bcast(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + N, 0xf, 0xf, false));
 }
 
-// Maximum over the 64 lanes, as a wave-uniform value: a running maximum along
-// each 16-lane row with DPP row shifts (a lane whose source is outside its row
-// keeps its own value), then the four row maxima (lanes 15, 31, 47, 63) read
-// into scalar registers. No LDS round trips.
+// Maximum over the 64 lanes of values that are >= 0 and not NaN, as a
+// wave-uniform value, on their bit patterns (which order the same way; a float
+// maximum would first quiet each operand): a running maximum along each 16-lane
+// row with DPP row shifts, then the four row maxima (lanes 15, 31, 47, 63) in
+// scalar registers. No LDS round trips.
 template <int SHIFT>
-__device__ __forceinline__ float row_shr_keep(float x) {
-  const int b = __builtin_bit_cast(int, x);
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, 0x110 + SHIFT, 0xf, 0xf, false));
+__device__ __forceinline__ unsigned row_shr_bits(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x110 + SHIFT, 0xf, 0xf, true);
 }
-__device__ __forceinline__ float wave_max_uniform(float x) {
-  x = fmaxf(x, row_shr_keep<1>(x));
-  x = fmaxf(x, row_shr_keep<2>(x));
-  x = fmaxf(x, row_shr_keep<4>(x));
-  x = fmaxf(x, row_shr_keep<8>(x));
-  const int b = __builtin_bit_cast(int, x);
-  const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 15));
-  const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 31));
-  const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 47));
-  const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 63));
-  return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+__device__ __forceinline__ unsigned umax(unsigned a, unsigned b) { return a > b ? a : b; }
+__device__ __forceinline__ float wave_max_uniform(float v) {
+  unsigned x = __builtin_bit_cast(unsigned, v);
+  x = umax(x, row_shr_bits<1>(x));
+  x = umax(x, row_shr_bits<2>(x));
+  x = umax(x, row_shr_bits<4>(x));
+  x = umax(x, row_shr_bits<8>(x));
+  const unsigned r0 = (unsigned)__builtin_amdgcn_readlane((int)x, 15);
+  const unsigned r1 = (unsigned)__builtin_amdgcn_readlane((int)x, 31);
+  const unsigned r2 = (unsigned)__builtin_amdgcn_readlane((int)x, 47);
+  const unsigned r3 = (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+  return __builtin_bit_cast(float, umax(umax(r0, r1), umax(r2, r3)));
 }
 
 }  // namespace gtr

@@ -1527,6 +1527,13 @@ def _maxdpp(w, i):
     w.vwrite(i.ops[0], vres(v, s, b), we)
 
 
+@handler('v_max_u32_dpp')
+def _maxudpp(w, i):
+    s, we = dpp_src(w, i, i.ops[1])
+    b = w.v32(i.ops[2], i)
+    w.vwrite(i.ops[0], vres(np.maximum(s.v, b.v), s, b), we)
+
+
 def mfma(i, w):
     # v_mfma_* dst, A, B, C : result opaque; defined iff every lane of A, B and C is defined
     dst, A, B, C = i.ops[:4]
@@ -1769,7 +1776,8 @@ def buffer_op(nregs, store):
     return h
 
 
-HANDLERS.update({'global_load_lds_dwordx4': gload_lds(4)})
+HANDLERS.update({'global_load_lds_dwordx4': gload_lds(4),
+                 'v_max3_u32': valu(lambda a, b, c: np.maximum(np.maximum(a, b), c), 3)})
 HANDLERS.update({'buffer_load_dword': buffer_op(1, False), 'buffer_load_dwordx2': buffer_op(2, False),
                  'buffer_load_dwordx4': buffer_op(4, False),
                  'buffer_store_dword': buffer_op(1, True), 'buffer_store_dwordx2': buffer_op(2, True),

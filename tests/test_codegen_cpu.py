@@ -190,9 +190,9 @@ class Launch:
     grouped look-back of the 16-bit kernel (FLAG_GROUP: every group aggregate
     is stored)."""
 
-    def __init__(self, vparts=1, desc=0, publish=1, flag=1, nxcd=0, group=0):
+    def __init__(self, vparts=1, desc=0, publish=1, flag=1, nxcd=0, group=0, segc=0):
         self.vparts, self.desc, self.publish, self.flag, self.nxcd = vparts, desc, publish, flag, nxcd
-        self.group = group
+        self.group, self.segc = group, segc
 
 
 def kernel_args(c: Shape, ln: Launch = Launch()):
@@ -232,11 +232,11 @@ def kernel_args(c: Shape, ln: Launch = Launch()):
     regions.insert(0, emu.Region("sync", ws + sync, ns * 16, "rw"))
     regions.insert(0, emu.Region("fault", ws, 256, "rw"))
     regions.append(emu.Region("kernarg", emu.KERNARG_BASE, KERNARG_BYTES, "r"))
-    kern = struct.pack("<7Q6iqifi4x6Qif2Qif6iIiI4x", q, k, v, g, o, s0, sf, DT[c.dt][0], DT[c.gdt][0],
+    kern = struct.pack("<7Q6iqifi4x6Qif2Qif6iIiiI", q, k, v, g, o, s0, sf, DT[c.dt][0], DT[c.gdt][0],
                        DT[c.odt][0], c.BH, c.H, c.W, c.L, c.NC, c.dk ** -0.5, SCAN[c.scan],
                        ws + agg, ws + rec, ws + states, ws + sync, ws + flags, ws,
                        1 if c.logits else 0, 1.0 / 16, z, nw, DT[c.zdt][0] if c.zdt else 0, 1e-5,
-                       c.dv, ln.vparts, ns, ln.desc, ln.publish, ln.nxcd, 8, ln.group, min((1 << 32) // c.H, (1 << 32) - 1))
+                       c.dv, ln.vparts, ns, ln.desc, ln.publish, ln.nxcd, 8, ln.group, ln.segc, min((1 << 32) // c.H, (1 << 32) - 1))
     assert len(kern) == KERNARG_BYTES
     return kern, regions
 
@@ -254,6 +254,8 @@ def mangled(kind: str, c: Shape) -> str:
     if kind in ("lean_split", "lean4_split"):
         occ = 4 if kind.startswith("lean4") else 3
         return f"_ZN3gtr15gla_lean_kernelILi{c.dk}ELi{c.dv // 2}ELi{c.chunk}ELi{DT[c.dt][0]}ELi{occ}EEEvNS_9GlaParamsE"
+    if kind == "seg":
+        return f"_ZN3gtr14gla_seg_kernelILi{c.dk}ELi{c.dv}ELi{DT[c.dt][0]}EEEvNS_9GlaParamsE"
     if kind in ("lean", "lean4"):
         occ = 4 if kind == "lean4" else 3
         return f"_ZN3gtr15gla_lean_kernelILi{c.dk}ELi{c.dv}ELi{c.chunk}ELi{DT[c.dt][0]}ELi{occ}EEEvNS_9GlaParamsE"
@@ -275,6 +277,9 @@ def work_groups(kind: str, c: Shape, ln: Launch):
         eb = (c.dk * c.dv + 255) // 256
         return [((x, bh, 0), 2) for x in sorted({0, eb - 1}) for bh in bhs]  # 128 threads
     ns = c.BH * ln.vparts
+    if kind == "seg":  # the first two segments of the first sequence, the last one of the last
+        nseg = (c.NC + ln.segc - 1) // ln.segc
+        return [((sg * ns + sq, 0, 0), nw) for sg, sq in sorted({(0, 0), (1 % nseg, 0), (nseg - 1, ns - 1)})]
     # one-launch kernels: the first chunks (and a group's last) of the first
     # sequence, the last chunk of the last sequence
     pairs = sorted({(cc, 0) for cc in cs if cc != c.NC - 1 or c.NC == 1} | {(c.NC - 1, ns - 1)})
@@ -303,13 +308,13 @@ LEAN = ("lean", "lean_n", "lean_x", "lean_i", "lean_xcd", "lean_split", "lean_g"
 CHECKS = [
     (Shape(1, 12, 40, 40, 64, 64, 64, "bf16", "bf16", "f32", "row", False, False),
      ("summary", "scan", "output") + CHAIN + ("chain_split",) + LEAN),
-    (Shape(8, 12, 40, 40, 64, 64, 64, "bf16", "bf16", "f32", "col_rev", True, True), ("output",) + CHAIN + ("lean_x", "lean_g")),
+    (Shape(8, 12, 40, 40, 64, 64, 64, "bf16", "bf16", "f32", "col_rev", True, True), ("output",) + CHAIN + ("lean_x", "lean_g", "seg")),
     (Shape(2, 9, 12, 20, 32, 32, 32, "bf16", "f32", "f32", "col", True, True), ("summary", "output") + CHAIN),
     (Shape(1, 2, 20, 20, 32, 64, 128, "bf16", "bf16", "bf16", "row_rev", False, False), ("output",) + CHAIN),
     (Shape(1, 6, 40, 40, 64, 64, 64, "f16", "f16", "f16", "row", False, False),
      CHAIN + ("chain_split", "lean_split")),
-    (Shape(1, 5, 9, 23, 32, 64, 64, "f16", "f32", "f32", "row_rev", True, True), ("lean", "lean_split", "lean4", "lean4_gs")),
-    (Shape(3, 3, 16, 16, 32, 32, 64, "bf16", "f32", "bf16", "col", False, True), ("lean_xcd",)),
+    (Shape(1, 5, 9, 23, 32, 64, 64, "f16", "f32", "f32", "row_rev", True, True), ("lean", "lean_split", "lean4", "lean4_gs", "seg")),
+    (Shape(3, 3, 16, 16, 32, 32, 64, "bf16", "f32", "bf16", "col", False, True), ("lean_xcd", "seg")),
     (Shape(1, 3, 7, 9, 64, 64, 128, "f16", "f32", "f32", "col", True, True), ("output",) + CHAIN + ("chain_split",)),
     (Shape(1, 2, 13, 11, 64, 64, 32, "f32", "f32", "f32", "row_rev", True, True), CHAIN + ("chain_split",)),
     (Shape(1, 2, 13, 11, 32, 32, 32, "f32", "f32", "f32", "row", False, True), ("summary", "output") + CHAIN),
@@ -317,7 +322,7 @@ CHECKS = [
     # gate fusion and the output-gate epilogue
     (Shape(1, 12, 40, 40, 64, 64, 64, "bf16", "bf16", "f32", "col", True, True, True, "bf16", True),
      ("summary", "output") + CHAIN + ("lean_i",)),
-    (Shape(2, 3, 8, 8, 64, 64, 64, "f16", "f32", "f16", "row", False, False, True, "f32", False), ("lean",)),
+    (Shape(2, 3, 8, 8, 64, 64, 64, "f16", "f32", "f16", "row", False, False, True, "f32", False), ("lean", "seg")),
     (Shape(1, 3, 7, 9, 32, 64, 32, "f16", "f32", "f16", "row_rev", False, False, True, "f32", False),
      ("summary", "output", "chain")),
 ]
@@ -358,6 +363,8 @@ def launches(kind: str, c: Shape):
         return [Launch(flag=FLAG_SUMMARY), Launch(desc=1, flag=FLAG_ALL)]
     if kind == "lean4_g":
         return [Launch(group=1, flag=FLAG_GROUP), Launch(group=1, flag=FLAG_NONE)]
+    if kind == "seg":  # segments of two and three chunks; nothing ready
+        return [Launch(flag=FLAG_SUMMARY, segc=2), Launch(flag=FLAG_SUMMARY, segc=3), Launch(flag=FLAG_NONE, segc=2)]
     if kind == "lean4_gs":
         return [Launch(vparts=2, group=1, flag=FLAG_GROUP | FLAG_ALL)]
     return [Launch()]

@@ -446,6 +446,78 @@ def test_fusions_parity(gtr, case, path):
         assert rel_err(sf, sf_ref) <= tol_for(wl.dtype, "f32")
 
 
+# segments of several chunks per work-group (16-bit inputs at chunk 64, grids of several rounds of
+# work-groups): ragged last segments and chunks, S0 and S_final, every dims pair, float32 gates, the fusions
+SEGMENTS = [
+    # B, heads, H, W, dk, dv, dtype, gdtype, odtype, scan, s0, final, fused
+    (8, 12, 41, 40, 64, 64, "f16", "f32", "f16", "col_rev", True, True, False),    # 96 sequences of 26 chunks
+    (4, 4, 67, 97, 32, 64, "f16", "f16", "f32", "col", True, True, False),         # 16 of 102, 35-token tail
+    (2, 6, 128, 65, 32, 32, "bf16", "bf16", "bf16", "row_rev", False, True, False),  # 12 of 130
+    (1, 9, 111, 113, 64, 64, "bf16", "f32", "f32", "row", False, False, True),     # 9 of 196, gate and epilogue
+    (1, 6, 127, 129, 32, 64, "f16", "f16", "f16", "col", False, False, True),      # 6 of 256, one-token tail
+]
+
+
+@pytest.mark.parametrize("case", range(len(SEGMENTS)))
+def test_segments_parity(gtr, case):
+    B, heads, H, W, dk, dv, dtype, gdtype, odtype, scan, s0, final, fused = SEGMENTS[case]
+    wl = edge_workload(B, heads, H, W, dk, dv, 64, dtype, gdtype, odtype, scan, s0, final, 7000 + case)
+    inp = make_inputs(wl)
+    rng = np.random.default_rng(7000 + case)
+    dev = torch.device("cuda")
+    kw, g_ref, z = {}, None, None
+    if fused:
+        inp["g"] = torch.from_numpy(rng.normal(2.0, 1.0, size=tuple(inp["g"].shape))).float().to(inp["g"].dtype)
+        z = torch.from_numpy(rng.normal(0.0, 1.5, size=(B, heads, H * W, dv))).float().to(torch_dtype(dtype))
+        kw = dict(gate_tau=16.0, out_gate=z.to(dev), norm_eps=1e-5)
+        g_ref = oracle.log_decay_from_logits(inp["g"], 16.0)
+    if gdtype != dtype:
+        inp["g"] = inp["g"].float()
+    q, k, v, g = (inp[n].to(dev) for n in ("q", "k", "v", "g"))
+    s0t = None if inp["s0"] is None else inp["s0"].to(dev)
+    ws = gtr.Workspace(dev)
+    o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], inp["g"] if g_ref is None else g_ref, inp["s0"],
+                               scale=wl.scale, H=H, W=W, scan=scan)
+    if fused:
+        o_ref = oracle.output_gate(o_ref, z, None, 1e-5)
+    run = lambda **m: gtr.gtr_gla_fwd(q, k, v, g, H=H, W=W, scan=scan, s0=s0t, want_final=final, path="fused",  # noqa: E731
+                                      o_dtype=torch_dtype(odtype), workspace=ws, **kw, **m)
+    for rep in range(2):  # the second call finds the flags as the first one left them
+        o, sf = run(check=True)
+        assert rel_err(o, o_ref) <= tol_for(dtype, odtype), (rep, rel_err(o, o_ref))
+        if final:
+            assert rel_err(sf, sf_ref) <= tol_for(dtype, "f32"), (rep, rel_err(sf, sf_ref))
+    # a wait of one poll: whatever is not NaN is right, and the call after it is whole again
+    o, _ = run(spin_limit=1)
+    torch.cuda.synchronize()
+    x = o.double().cpu().numpy()
+    rows = np.isnan(x).any(-1)
+    assert (np.isnan(x).all(-1) == rows).all() and rel_err(x[~rows], o_ref[~rows]) <= tol_for(dtype, odtype)
+    assert not rows.any() or gtr.gtr_gla_workspace_fault(ws.buf) & 1
+    o, _ = run()
+    assert rel_err(o, o_ref) <= tol_for(dtype, odtype)
+
+
+def test_segments_report_values_outside_the_fp16_range(gtr):
+    """A bf16 value beyond the fp16 range, in segments: NaN from its chunk on in
+    its sequence, everything before it and every other sequence right."""
+    wl = WORKLOADS["batched"].with_(s0_std=None, want_final=True)
+    inp = make_inputs(wl)
+    inp["v"][3, 5, 700, 3] = 1.0e6  # chunk 10 of the sequence
+    dev = torch.device("cuda")
+    q, k, v, g = (inp[n].to(dev) for n in ("q", "k", "v", "g"))
+    ws = gtr.Workspace(dev)
+    o, sf = gtr.gtr_gla_fwd(q, k, v, g, H=wl.H, W=wl.W, want_final=True, o_dtype=torch.float32, workspace=ws)
+    torch.cuda.synchronize()
+    assert gtr.gtr_gla_workspace_fault(ws.buf) == 2
+    o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], inp["g"], None, scale=wl.scale, H=wl.H, W=wl.W)
+    x, s = o.double().cpu().numpy(), sf.double().cpu().numpy()
+    assert np.isnan(x[3, 5, 640:]).all() and np.isnan(s[3, 5]).all()
+    x[3, 5, 640:], s[3, 5] = 0.0, 0.0
+    o_ref[3, 5, 640:], sf_ref[3, 5] = 0.0, 0.0
+    assert rel_err(x, o_ref) <= 2e-3 and rel_err(s, sf_ref) <= 2e-3
+
+
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("dtype,chunk", [("f16", 64), ("bf16", 32), ("f32", 64), ("f16", 128)])
 def test_gate_logits_ragged_final_state(gtr, dtype, chunk, path):
