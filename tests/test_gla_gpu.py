@@ -743,6 +743,26 @@ def test_default_workspaces_are_per_stream(gtr):
             assert torch.equal(outs[i][n], refs[i]), (i, n)
 
 
+@pytest.mark.parametrize("fault", ["cpu", "strided", "tokens", "width", "heads", "f32", "bf16"])
+@pytest.mark.parametrize("name", ["q", "k", "v", "g"])
+def test_binding_refuses_a_wrong_operand(gtr, name, fault):
+    """Each operand on the wrong device, not contiguous, of another shape or of another type is refused before
+    anything is launched; a float32 g with 16-bit q, k, v is taken."""
+    mk = lambda d: torch.zeros((1, 2, 16, d), dtype=torch.float16, device="cuda")
+    ops = {"q": mk(32), "k": mk(32), "v": mk(64), "g": mk(32)}
+    t = ops[name]
+    ops[name] = {"cpu": lambda: t.cpu(), "strided": lambda: t.transpose(1, 2).contiguous().transpose(1, 2),
+                 "tokens": lambda: t[:, :, :15].contiguous(), "width": lambda: t[..., :16].contiguous(),
+                 "heads": lambda: t[:, :1].contiguous(), "f32": lambda: t.float(), "bf16": lambda: t.bfloat16()}[fault]()
+    call = lambda: gtr.gtr_gla_fwd(ops["q"], ops["k"], ops["v"], ops["g"], H=4, W=4)
+    if (name, fault) == ("g", "f32"):
+        assert torch.equal(call()[0], torch.zeros_like(ops["v"]))
+    else:  # a v of width 16 passes as an operand, (d_k, d_v) = (32, 16) is refused by the library
+        with pytest.raises((ValueError, gtr.GtrError)):
+            call()
+    torch.cuda.synchronize()
+
+
 # ---------------------------------------------------------------------------
 # Spatial SwiGLU (Sec. 3.1), against the oracle's definition
 # ---------------------------------------------------------------------------
