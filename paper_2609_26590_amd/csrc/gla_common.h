@@ -491,6 +491,22 @@ __device__ __forceinline__ int wait_groups(const GlaParams& P, const T& ch, int 
   }
 }
 
+// The end of a one-launch call, per sequence: every work-group adds itself to
+// the sequence's count once it reads no flag any more and its own flags are up
+// (its stores and atomics so far acknowledged), and the last of the n leaves the
+// flags and the count zeroed for the next call. count_out: one lane, returns the
+// count before it; clear_if_last: that lane's whole wave.
+__device__ __forceinline__ unsigned count_out(const GlaParams& P, int seq) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  return __hip_atomic_fetch_add(P.sync + 4 * seq, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void clear_if_last(const GlaParams& P, int seq, int n, unsigned before, int lane) {
+  if (__builtin_amdgcn_readfirstlane(before) != (unsigned)n - 1) return;
+  unsigned* fl = P.flags + (size_t)seq * kMaxChainChunks;
+  for (int j = lane; j < n; j += kWave) __hip_atomic_store(&fl[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) __hip_atomic_store(P.sync + 4 * seq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The one-launch kernels for 16-bit inputs at chunk 64 (gla_lean.hip): the
 // whole-width kernel and the value-split one (d_v / 2 columns; null unless
 // d_v = 64). Returns false (both null) for every other shape or dtype.

@@ -921,6 +921,10 @@ __global__ void __launch_bounds__(tile_threads(C)) gla_chain_kernel(GlaParams P)
     }
   }
 
+  // This work-group reads no flag any more: it is counted out here, and the
+  // count's way to memory and back passes during the readout and the stores.
+  unsigned left = 0;
+  if (threadIdx.x == 0) left = count_out(P, seq);
   if (c > 0 || P.s0) {
     ch.state_tile(sm, acc, mx);
     __syncthreads();  // state tile complete
@@ -929,16 +933,7 @@ __global__ void __launch_bounds__(tile_threads(C)) gla_chain_kernel(GlaParams P)
   // every wave is past the intra part (the exchange above): the k rows in buf
   // are dead, so the output tile needs no barrier before it
   ch.template store<false>(P, sm, bh, c, O, rz, poison);
-
-  if (threadIdx.x == 0) {
-    unsigned* done = P.sync + 4 * seq;
-    const unsigned prev = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == (unsigned)NC - 1) {  // last one out: leave the flags and the count zeroed
-      unsigned* fl = P.flags + (size_t)seq * kMaxChainChunks;
-      for (int j = 0; j < NC; ++j) __hip_atomic_store(&fl[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
+  if (threadIdx.x < kWave) clear_if_last(P, seq, NC, left, ch.lane);
 }
 
 __global__ void zero_fill_kernel(uint4* p, size_t n16) {

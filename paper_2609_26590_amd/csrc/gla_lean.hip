@@ -854,6 +854,11 @@ gla_lean_kernel(GlaParams P) {
     }
   }
 
+  // This work-group reads no flag any more: it is counted out here, and the
+  // count's way to memory and back (0.5 us) passes during the readout and the
+  // stores.
+  unsigned left = 0;
+  if (threadIdx.x == 0) left = count_out(P, seq);
   if (c > 0 || P.s0) {
     // the key tile (which the state tile overwrites) is dead: every wave is
     // past its summary and intra part (the exchange above)
@@ -862,16 +867,7 @@ gla_lean_kernel(GlaParams P) {
     ch.readout(sm, O);
   }
   ch.store(P, bh, c, O, rz, poison);
-
-  if (threadIdx.x == 0) {
-    unsigned* done = P.sync + 4 * seq;
-    const unsigned prev = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == (unsigned)NC - 1) {  // last one out: leave the flags and the count zeroed
-      unsigned* fl = P.flags + (size_t)seq * kMaxChainChunks;
-      for (int j = 0; j < NC; ++j) __hip_atomic_store(&fl[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
+  if (ch.w == 0) clear_if_last(P, seq, NC, left, ch.lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1139,15 +1135,12 @@ gla_seg_kernel(GlaParams P) {
       *reinterpret_cast<f4*>(P.s_final + ((size_t)bh * DK + row_of(m)) * DV + 16 * jb + 4 * ch.g) = S[m];
     }
   }
+  unsigned left = 0;
   if (threadIdx.x == 0) {
     if (fault) __hip_atomic_fetch_or(P.fault, fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned* done = P.sync + 4 * seq;
-    const unsigned prev = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == (unsigned)nseg - 1) {  // last one out: leave the flags and the count zeroed
-      for (int j = 0; j < nseg; ++j) __hip_atomic_store(&fl[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    left = count_out(P, seq);
   }
+  if (ch.w == 0) clear_if_last(P, seq, nseg, left, ch.lane);
 }
 
 template <int DK, int DV, int IN>
