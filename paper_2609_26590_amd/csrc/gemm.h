@@ -159,6 +159,22 @@ __device__ __forceinline__ void piece_stats(const w4& v, float one, float shift,
     q = fmaf(d1, d1, q);
   }
 }
+// Adds a piece's 8 elements, in their order.
+template <int BDT>
+__device__ __forceinline__ void piece_sum(const w4& v, float one, float& s) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const unsigned u = v[e];
+    if constexpr (BDT == GTR_F16) {
+      const unsigned short lo = (unsigned short)(u & 0xffffu), hi = (unsigned short)(u >> 16);
+      s = fmaf((float)__builtin_bit_cast(_Float16, lo), one, s);
+      s = fmaf((float)__builtin_bit_cast(_Float16, hi), one, s);
+    } else {
+      s += __builtin_bit_cast(float, u << 16);
+      s += __builtin_bit_cast(float, u & 0xffff0000u);
+    }
+  }
+}
 template <int ADT>
 __device__ __forceinline__ float first_elem(unsigned u) {
   const unsigned short lo = (unsigned short)(u & 0xffffu);
@@ -166,48 +182,52 @@ __device__ __forceinline__ float first_elem(unsigned u) {
 }
 
 // Mean and 1 / sqrt(var + eps) of the BM rows of A from row mb on, over K
-// columns, into st: 16 lanes per row, BM / NW rows per wave, from memory (the
-// rows the ring reads next). Squares are taken about the row's first element,
+// columns, into st: 8 lanes per row (lane l takes pieces l, l + 8, .., the order of
+// LN = 1's sums), BM / NW rows per wave, from memory (the rows the ring reads next). Squares are taken about the row's first element,
 // so that a mean large next to the spread costs no precision.
 template <int ADT, int BM, int NW>
 __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, int lane, f2* st) {
-  constexpr int RW = BM / NW, G = RW % 16 == 0 ? 4 : 2, U = 3;  // rows per wave; groups of 4 rows, pieces in flight
-  static_assert(RW % (4 * G) == 0, "rows split evenly over the waves");
-  const int l = lane & 15, np = g.K / 8;
+  constexpr int RW = BM / NW, G = RW % 16 == 0 ? 2 : 1, U = 6;  // rows per wave; groups of 8 rows, pieces in flight
+  static_assert(RW % (8 * G) == 0, "rows split evenly over the waves");
+  const int l = lane & 7, np = g.K / 8;
   const float inv = 1.f / (float)g.K;
   float one = 1.f;
   asm volatile("" : "+v"(one));
 #pragma unroll 1
-  for (int r0 = wave * RW; r0 < (wave + 1) * RW; r0 += 4 * G) {
+  for (int r0 = wave * RW; r0 < (wave + 1) * RW; r0 += 8 * G) {
     const w4* p[G];
     float sh[G], s[G], q[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       p[u] = reinterpret_cast<const w4*>(static_cast<const unsigned short*>(g.A) +
-                                         (int64_t)min(mb + r0 + 4 * u + (lane >> 4), g.M - 1) * g.K);
+                                         (int64_t)min(mb + r0 + 8 * u + (lane >> 3), g.M - 1) * g.K);
       sh[u] = s[u] = q[u] = 0.f;
     }
 #pragma unroll 1
-    for (int c = 0; c < np; c += 16 * U) {
+    for (int c = 0; c < np; c += 8 * U) {
       w4 v[G][U];
 #pragma unroll
       for (int u = 0; u < G; ++u)
 #pragma unroll
-        for (int x = 0; x < U; ++x) v[u][x] = p[u][min(c + 16 * x + l, np - 1)];
+        for (int x = 0; x < U; ++x) v[u][x] = p[u][c + 8 * x + l < np ? c + 8 * x + l : l];
       if (c == 0)
 #pragma unroll
-        for (int u = 0; u < G; ++u) sh[u] = row_bcast<0>(first_elem<ADT>(v[u][0][0]));
+        for (int u = 0; u < G; ++u) sh[u] = __shfl(first_elem<ADT>(v[u][0][0]), lane & ~7, kWave);
 #pragma unroll
       for (int x = 0; x < U; ++x)
-        if (c + 16 * x + l < np)
+        if (c + 8 * x < np)  // K is a multiple of 64: all lanes or none
 #pragma unroll
           for (int u = 0; u < G; ++u) piece_stats<ADT>(v[u][x], one, sh[u], s[u], q[u]);
     }
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const float a = row_bcast<15>(row_inclusive_scan(s[u])) * inv;
-      const float b = row_bcast<15>(row_inclusive_scan(q[u])) * inv;
-      if (l == 0) st[r0 + 4 * u + (lane >> 4)] = f2{sh[u] + a, rsqrtf(fmaxf(b - a * a, 0.f) + g.ln_eps)};
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) {
+        s[u] += __shfl_xor(s[u], o, kWave);
+        q[u] += __shfl_xor(q[u], o, kWave);
+      }
+      const float m1 = s[u] * inv;
+      if (l == 0) st[r0 + 8 * u + (lane >> 3)] = f2{sh[u] + m1, rsqrtf(fmaxf(q[u] * inv - m1 * m1, 0.f) + g.ln_eps)};
     }
   }
 }
@@ -241,7 +261,7 @@ __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, i
 // LN: every row of A is normalised over its K columns (A' = (A - mu) / sqrt(var
 // + eps), a layer normalisation without affine weights, which the caller folds
 // into B and the bias) inside the product: the MFMAs multiply the raw A, the
-// row sums of B come from one more MFMA per operand (against ones), and the
+// row sums of B are taken from the operands as they are read, and the
 // epilogue forms rs_m (C_mn - mu_m rowsum_n), which is A' B^T in real arithmetic.
 // The statistics come from the operands as they are read (LN = 1: no extra
 // load, for small tiles and short chains) or from a pass over the rows before
@@ -252,7 +272,7 @@ __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, i
 // dispatch), and each XCD takes a contiguous range of the order (slice, row
 // block, column group), column groups fastest: the work-groups that read the
 // same rows of A share one XCD's L2.
-template <int ADT, int BDT, int MT, int BM, int BN, int WM, int WN, int S, int LN>
+template <int ADT, int BDT, int MT, int BM, int BN, int WM, int WN, int S, int LN, int KH>
 __global__ void __launch_bounds__(64 * WM * WN)
 __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(GemmArgs g) {
   typedef Operand<ADT, MT> OA;
@@ -327,10 +347,8 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
     }
   };
 
-  f4 acc[TI][TJ], cs[TJ];  // cs: row sums of B, every row of a tile the same
-  typename OB::T ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = 1.f;
+  f4 acc[KH][TI][TJ];  // KH = 2: one set for each 32-deep half of a step
+  float bs[TJ][2];     // LN: sums of B's row r16 of tile j over this lane's pieces kq and 4 + kq
 
   float sh[TI], sa[TI], sq[TI];  // LN = 1: row statistics from the operands as they are read
   float one = 1.f;
@@ -355,11 +373,11 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
       for (int i = 0; i < TI; ++i) {
         const typename OA::T fa = OA::get(ra[i]);
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = mfma(fb[j], fa, acc[i][j]);  // C^T tiles
+        for (int j = 0; j < TJ; ++j) acc[h % KH][i][j] = mfma(fb[j], fa, acc[h % KH][i][j]);  // C^T tiles
       }
       if constexpr (LN != 0) {
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) cs[j] = mfma(fb[j], ones, cs[j]);
+        for (int j = 0; j < TJ; ++j) piece_sum<BDT>(rb[j], one, bs[j][h]);
       }
       if constexpr (LN == 1) {  // every (row block, half) of A is read by WN waves: wave wni takes its share
 #pragma unroll
@@ -385,9 +403,9 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
   for (int t = 0; t < tiles; ++t) {
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
-      cs[j] = f4{0.f, 0.f, 0.f, 0.f};
+      bs[j][0] = bs[j][1] = 0.f;
 #pragma unroll
-      for (int i = 0; i < TI; ++i) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < KH * TI; ++q) acc[q / TI][q % TI][j] = f4{0.f, 0.f, 0.f, 0.f};
     }
     for (int k = 0; k < steps; ++k, ++f) {
       // this step's stage has landed (the stages after it may be in flight), and
@@ -446,6 +464,21 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
     const unsigned tokens = hmc ? (unsigned)g.c_tokens : 1u, cdim = hmc ? (unsigned)g.c_dim : 1u;
     const unsigned hd = hmc ? (unsigned)(g.c_heads * g.c_dim) : 1u, img = (unsigned)g.M / tokens;
     int64_t coloff[TJ];
+    f4 cs[TJ];  // LN: row sums of B for the lane's four columns
+    if constexpr (LN != 0) {
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        float s2[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          s2[h] = bs[j][h] + __shfl_xor(bs[j][h], 16, kWave);
+          s2[h] += __shfl_xor(s2[h], 32, kWave);
+        }
+        const float sum = s2[0] + s2[1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[j][e] = __shfl(sum, 4 * kq + e, kWave);
+      }
+    }
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
       const unsigned n0 = (unsigned)(nb + wn + 16 * j + 4 * kq);
@@ -463,7 +496,9 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
       for (int j = 0; j < TJ; ++j) {
         const int n0 = nb + wn + 16 * j + 4 * kq;
         const int64_t off = rowoff + coloff[j];
-        float x[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        f4 sum = acc[0][i][j];
+        if constexpr (KH == 2) sum += acc[1][i][j];
+        float x[4] = {sum[0], sum[1], sum[2], sum[3]};
         if constexpr (LN != 0) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[e] = st[1] * (x[e] - st[0] * cs[j][e]);

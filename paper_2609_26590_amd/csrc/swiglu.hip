@@ -324,10 +324,10 @@ static int pick_tile(int64_t M, int N, bool ln) {
   return best;
 }
 
-template <int ADT, int BDT, int MT, int BM, int BN, int WM, int WN, int S, int LN>
+template <int ADT, int BDT, int MT, int BM, int BN, int WM, int WN, int S, int LN, int KH = 1>
 static void launch_tile(const GemmArgs& g, hipStream_t stream) {
   const int64_t wgs = (int64_t)((g.M + BM - 1) / BM) * ((g.N / BN + g.cols - 1) / g.cols) * g.ksplit;
-  hipLaunchKernelGGL((gemm_ring_kernel<ADT, BDT, MT, BM, BN, WM, WN, S, LN>), dim3((unsigned)wgs), dim3(64 * WM * WN), 0,
+  hipLaunchKernelGGL((gemm_ring_kernel<ADT, BDT, MT, BM, BN, WM, WN, S, LN, KH>), dim3((unsigned)wgs), dim3(64 * WM * WN), 0,
                      stream, g);
 }
 
@@ -348,6 +348,12 @@ static int pick_cols(int64_t M, int N, const GemmTile& t) {
   return best;
 }
 
+// Grids of fewer than kCUs tiles leave one work-group (four waves) on a CU, and
+// its K loop is a chain of dependent steps: there the two 32-deep halves of a
+// step are summed apart (KH = 2), which cuts the chain of dependent MFMAs and of
+// float32 additions in half and rounds as the same product with its halves on
+// separate waves does. The registers are free at that size; larger grids gain
+// nothing from it.
 template <int ADT, int BDT, int MT, bool LN>
 static void launch_gemm(GemmArgs g, hipStream_t stream) {
   const int t = g.ksplit > 1 ? 3 : pick_tile(g.M, g.N, LN);
@@ -358,6 +364,8 @@ static void launch_gemm(GemmArgs g, hipStream_t stream) {
     launch_tile<ADT, BDT, MT, 64, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
   else if (!LN && t == 2)
     launch_tile<ADT, BDT, MT, 64, 128, 2, 2, 2, 0>(g, stream);
+  else if (((int64_t)g.M + 63) / 64 * (g.N / 64) * g.ksplit < kCUs)
+    launch_tile<ADT, BDT, MT, 64, 64, 2, 2, LN ? 2 : 3, LN ? 1 : 0, 2>(g, stream);
   else
     launch_tile<ADT, BDT, MT, 64, 64, 2, 2, LN ? 2 : 3, LN ? 1 : 0>(g, stream);
 }

@@ -516,7 +516,7 @@ def test_swiglu_gemm_addresses(adt, bdt, mt, bn, M, N, K, cdt, ks, epi):
         names = [n for n in emu.kernel_names(text) if "gemm_ring_kernel" in n and
                  f"ILi{adt}ELi{bdt}ELi{mt}ELi{bm}ELi{tn}ELi{wm}ELi{wn}E" in n]
         for name in names:
-            ln = int(re.search(r"ELi(\d)EEEv", name).group(1))
+            ln = int(re.search(r"ELi(\d)ELi\dEEEv", name).group(1))
             if (ln > 0) != bool(epi & 16):
                 continue
             seen += 1
