@@ -92,7 +92,8 @@ def schedule_of(wl, path):
 KERNEL_OF = {"inline": "gla_lean_kernel for 16-bit inputs at chunk 64, else gla_chain_kernel (one launch, "
                        "look-back over summaries: the whole call is this kernel)",
              "fused": "gla_lean_kernel for 16-bit inputs at chunk 64, else gla_chain_kernel (one launch, "
-                      "look-back to inclusive states: the whole call is this kernel)",
+                      "look-back to inclusive states: the whole call is this kernel); grids of many chunks per CU: "
+                      "gla_seg_kernel (segments of several chunks per work-group)",
              "staged": "one gtr_gla_fwd call (summary + scan + output kernels)"}
 
 
