@@ -72,8 +72,14 @@ struct Lean {
   static constexpr int kFk = 1;    // 2^(sum of the totals after R): summary
   static constexpr int kFh = 2;    // 2^(-T_R / 2): diagonal mid-point
   static constexpr int kFoff = 3;  // + J: 2^(sum of the totals between J and R), J < R
+  // spans of the diagonal tiers in base-2 units
+  static constexpr float kSpanF16b = kSpanF16 * kLog2e, kSpanF32b = kSpanF32 * kLog2e;
 
   struct Smem {
+    // The tiers from the wave's maxima, compared where they are used: as two flags
+    // taken early the kernel at four work-groups per CU spills 12 registers (48
+    // sequences of 25 chunks at d_k 64, inputs from HBM: 37.2 us against 34.8).
+    static constexpr bool kBallot = false;
     union alignas(16) {
       _Float16 ke[C * RP];   // k 2^(T_R - a), token-major
       _Float16 st[DK * SPp];  // S_[c] / tsc, key-dim-major (after the look-back)
@@ -89,13 +95,14 @@ struct Lean {
   };
 
   int w, lane, tr, g, r;
-  unsigned tok;      // spatial index of this lane's token (0 past the end of the sequence)
-  bool tok_ok;       // the position exists
   float qh[KS][8];   // q 2^(a_r)
   float ke[KS][8];   // k 2^(T_R - a_r)
   h8 qt[KS];         // q 2^(A_r), the readout operand
-  bool diag16;       // wave-uniform: the diagonal block's factors and operands fit fp16
-  bool diag32;       // wave-uniform: its factors fit float32
+  // What picks the diagonal block's tier, wave-uniform: the widest log2-decay
+  // across the sub-chunk and its largest |q|, |k|, or (kBallot) whether the
+  // factors and operands fit fp16, and the factors float32
+  float spanmax, absmax;
+  bool diag16, diag32;
   float usc;         // chunk-uniform: U_c travels as fp16(U_c / usc)
   float pup;         // wave-uniform: the fp16 score tile holds P / pup
   float tsc;         // chunk-uniform: the fp16 state tile holds S_[c] / tsc
@@ -181,9 +188,7 @@ struct Lean {
   // that is handed over.
   template <bool WITHQ, bool SCALES, class S>
   __device__ __forceinline__ void tokens(const GlaParams& P, S& sm, const Rows& x) {
-    tok = x.tok;
-    tok_ok = x.ok;
-    const bool valid = tok_ok;
+    const bool valid = x.ok;
     // log2-decays and their inclusive sums within the sub-chunk
     float a[KS][8], tot[KS][8];
     float spn = 0.f, am = 0.f, vm = 0.f;
@@ -244,14 +249,16 @@ struct Lean {
       }
       *reinterpret_cast<h8*>(&sm.v[r * VP + 32 * s + 8 * g]) = vh;
     }
-    if constexpr (WITHQ) {
-      constexpr float kSpanF16b = kSpanF16 * kLog2e, kSpanF32b = kSpanF32 * kLog2e;
+    if constexpr (WITHQ && S::kBallot) {
       diag16 = __builtin_amdgcn_ballot_w64(!(spn <= kSpanF16b && am <= 256.f)) == 0;
       diag32 = __builtin_amdgcn_ballot_w64(!(spn <= kSpanF32b)) == 0;
+    } else if constexpr (WITHQ) {
+      spanmax = wave_max_uniform(spn);
+      absmax = wave_max_uniform(am);
     }
     range_bad = false;
     if constexpr (SCALES) {
-      am = wave_max_uniform(am);
+      am = WITHQ ? absmax : wave_max_uniform(am);
       vm = wave_max_uniform(vm);
       if (lane == 0) {
         sm.M[w][0] = am;
@@ -373,8 +380,8 @@ struct Lean {
   // mid-point factors: P^T[j][r] = sum_d q_r k_j exp(a_r - a_j), j <= r, from
   // the raw q, k, g of the sub-chunk (reloaded; rare).
   __device__ __forceinline__ f4 exact_diagonal(const GlaParams& P, float (*pt)[17], int bh, int c) const {
-    const unsigned t = tok;
-    const bool valid = tok_ok;
+    bool valid;
+    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
     const int64_t kb = ((int64_t)bh * P.L + t) * DK;
     float qx[KS][8], kx[KS][8], ax[KS][8];
 #pragma unroll
@@ -448,7 +455,7 @@ struct Lean {
     // stay well inside the fp16 range, float32 operands up to e^30, else exact
     {
       f4 D = {0.f, 0.f, 0.f, 0.f};
-      if (diag16) {
+      if (S::kBallot ? diag16 : spanmax <= kSpanF16b && absmax <= 256.f) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const f4 lo = *reinterpret_cast<const f4*>(&sm.F[w][kFh][32 * s + 8 * g]);
@@ -463,7 +470,7 @@ struct Lean {
           }
           D = mma32(a, b, D);
         }
-      } else if (diag32) {
+      } else if (S::kBallot ? diag32 : spanmax <= kSpanF32b) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const f4 lo = *reinterpret_cast<const f4*>(&sm.F[w][kFh][32 * s + 8 * g]);
@@ -601,8 +608,9 @@ struct Lean {
 
   // The output-gate pre-activation for this lane's row and columns (loaded
   // early, with the other inputs; only when P.gate is set).
-  __device__ __forceinline__ void prefetch_gate(const GlaParams& P, int bh, Raw (&rz)[VB]) const {
-    const unsigned t = tok;
+  __device__ __forceinline__ void prefetch_gate(const GlaParams& P, int bh, int c, Raw (&rz)[VB]) const {
+    bool valid;
+    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
 #pragma unroll
     for (int jb = 0; jb < VB; ++jb) {
       const int64_t off = ((int64_t)bh * P.L + t) * P.dvp + 16 * jb + 4 * g;
@@ -620,8 +628,8 @@ struct Lean {
   // columns per value block; `poison` stores NaN instead.
   __device__ __forceinline__ void store(const GlaParams& P, int bh, int c, const f4 (&O)[VB], const Raw (&rz)[VB],
                                         bool poison) const {
-    const unsigned t = tok;
-    const bool valid = tok_ok;
+    bool valid;
+    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
     const float mul = poison ? __builtin_nanf("") : P.scale;
     float x[VB][4];
 #pragma unroll
@@ -773,7 +781,7 @@ gla_lean_kernel(GlaParams P) {
   // the output gate's loads overlap the exchange, the state tile and the
   // readout (issued earlier they would hold registers through every phase)
   Raw rz[T::VB];
-  if (P.gate) ch.prefetch_gate(P, bh, rz);
+  if (P.gate) ch.prefetch_gate(P, bh, c, rz);
   const bool okw = base >= -1;
   // one exchange makes the outcome uniform (a wait that ran out, or a NaN
   // state handed over by a poisoned chunk before it, poisons everything this
@@ -896,6 +904,10 @@ gla_lean_kernel(GlaParams P) {
 template <class L>
 struct SegSmem {
   static constexpr int DK = L::kDK, DV = L::kDV, C = L::NW * 16;
+  // The diagonal tiers as two flags from one ballot each: 2 % faster at d_k 32 than
+  // the maxima, 3 to 8 % slower at d_k 64, where they make the kernel spill 28 to
+  // 35 registers.
+  static constexpr bool kBallot = DK == 32;
   union alignas(16) {
     struct {
       _Float16 ke[C * L::RP];  // k 2^(T_R - a), token-major
@@ -1114,7 +1126,7 @@ gla_seg_kernel(GlaParams P) {
     ch.factors(sm);  // its barrier also completes the state tile
     if (PF && c + 1 < c1) ch.template fetch<true>(P, bh, c + 1, x);
     Raw rz[T::VB];
-    if (P.gate) ch.prefetch_gate(P, bh, rz);
+    if (P.gate) ch.prefetch_gate(P, bh, c, rz);
     f4 O[T::VB];
     ch.intra(P, sm, bh, c, O);
 #pragma unroll

@@ -383,6 +383,20 @@ def asm_text():
     return device_asm()
 
 
+def vector_spills(text: str, sub: str) -> dict:
+    """Vector registers spilled to memory per kernel whose name holds `sub`."""
+    found = re.findall(r"\.name:\s+(_ZN3gtr\w*%s\w*)\n.*?\.vgpr_spill_count:\s+(\d+)" % sub, text, re.S)
+    assert found
+    return {name: int(n) for name, n in found}
+
+
+@pytest.mark.parametrize("sub", ["gla_lean_kernel", "gla_seg_kernel"])
+def test_one_launch_kernels_spill_nothing(asm_text, sub):
+    """The 16-bit kernels run at the register count of a fixed occupancy; a
+    spilled register goes to memory and back in every chunk."""
+    assert {n: c for n, c in vector_spills(asm_text, sub).items() if c} == {}
+
+
 _JOBS = {}  # kernel listings shared with the forked workers
 
 
