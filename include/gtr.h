@@ -118,9 +118,9 @@ typedef enum {
                           16 chunks: the last chunk of each group also hands over
                           the group's aggregate, and a chunk sums the summaries
                           of its own group and then one aggregate per earlier
-                          group. Where the chunks are several times the
-                          work-groups that fit, a work-group takes a segment of
-                          consecutive chunks instead: it hands over the segment's
+                          group. Where the grid is many chunks per CU (and
+                          gtr_gla_segment_chunks says so), a work-group takes a
+                          segment of consecutive chunks instead: it hands over the segment's
                           aggregate, sums the aggregates of the segments before
                           it and carries the state through its own chunks.
                           At most 1024 sequences of 256 chunks.                     */
@@ -262,6 +262,14 @@ int gtr_gla_schedule(const gtr_gla_args* args);
  * computes what, not the arithmetic of any output element.
  */
 int gtr_gla_value_parts(const gtr_gla_args* args);
+
+/*
+ * gtr_gla_segment_chunks - consecutive chunks per work-group in the schedule
+ * gtr_gla_schedule reports: 1 or more where FUSED runs in segments, 0 where every
+ * chunk has a work-group of its own; -1 where gtr_gla_schedule gives -1.
+ * Host-only, like gtr_gla_schedule.
+ */
+int gtr_gla_segment_chunks(const gtr_gla_args* args);
 
 /*
  * Spatial SwiGLU (Sec. 3.1, "Spatial SwiGLU"):

@@ -39,7 +39,7 @@ _DT = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 _DT_BACK = {F32: torch.float32, F16: torch.float16, BF16: torch.bfloat16}
 
 EXPORTS = ("gtr_scan_permute", "gtr_gla_workspace_size", "gtr_gla_workspace_init", "gtr_gla_fwd", "gtr_gla_fwd_noalloc",
-           "gtr_gla_schedule", "gtr_gla_value_parts", "gtr_gla_workspace_fault", "gtr_status_string", "gtr_spatial_swiglu_workspace_size",
+           "gtr_gla_schedule", "gtr_gla_value_parts", "gtr_gla_segment_chunks", "gtr_gla_workspace_fault", "gtr_status_string", "gtr_spatial_swiglu_workspace_size",
            "gtr_spatial_swiglu", "gtr_gemm", "gtr_layernorm", "gtr_heads_split", "gtr_heads_merge", "gtr_add")
 
 
@@ -118,6 +118,8 @@ def load(path: Optional[str] = None) -> ctypes.CDLL:
     lib.gtr_gla_schedule.restype = ctypes.c_int
     lib.gtr_gla_value_parts.argtypes = [ctypes.POINTER(GlaArgs)]
     lib.gtr_gla_value_parts.restype = ctypes.c_int
+    lib.gtr_gla_segment_chunks.argtypes = [ctypes.POINTER(GlaArgs)]
+    lib.gtr_gla_segment_chunks.restype = ctypes.c_int
     lib.gtr_gla_workspace_fault.argtypes = [P, ctypes.c_size_t]
     lib.gtr_gla_workspace_fault.restype = ctypes.c_int
     lib.gtr_status_string.argtypes = [ctypes.c_int]
@@ -371,6 +373,18 @@ def gtr_gla_value_parts(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, g: to
     r = int(load().gtr_gla_value_parts(ctypes.byref(args)))
     if r not in (1, 2):
         raise GtrError("gtr_gla_value_parts", 3)
+    return r
+
+
+def gtr_gla_segment_chunks(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, g: torch.Tensor, *, H: int, W: int,
+                           chunk: int = 64, path: str = "auto", gate_tau: Optional[float] = None,
+                           out_gate: Optional[torch.Tensor] = None) -> int:
+    """Chunks per work-group where that schedule runs in segments, 0 where every chunk has its own work-group."""
+    o = torch.empty((0,), dtype=q.dtype, device=q.device)
+    args = make_args(q, k, v, g, H=H, W=W, scale=1.0, chunk=chunk, o=o, path=path, gate_tau=gate_tau, out_gate=out_gate)
+    r = int(load().gtr_gla_segment_chunks(ctypes.byref(args)))
+    if r < 0:
+        raise GtrError("gtr_gla_segment_chunks", 3)
     return r
 
 

@@ -1088,8 +1088,8 @@ struct Plan {
 //   * the value split (d_v = 64 in two halves, no output gate: its RMSNorm needs
 //     whole rows) when the doubled grid still gives every work-group a CU of
 //     its own;
-//   * where the grid is several rounds of work-groups, FUSED on the 16-bit
-//     kernel runs segments of several chunks per work-group (gla_seg_kernel);
+//   * where the grid is several rounds of work-groups, FUSED on the 16-bit kernel
+//     runs segments of several chunks per work-group (segment_chunks);
 //   * the chunk-major grid, in descending chunk order when every work-group is
 //     resident at once (ascending for the grouped look-back).
 // An explicit path that does not fit is GTR_ERR_UNSUPPORTED; STAGED always fits.
@@ -1102,7 +1102,45 @@ constexpr int64_t kGroupMinChunks = kInlineMaxChunks + 1;
 
 constexpr int64_t kSegMax = 64;  // segments per sequence: one ballot of their flags
 
-static gtr_status plan_call(const GlaShape& s, int path, bool gate, const KernelSet& ks, Plan* pl) {
+// Chunks per work-group of the segment kernel with `slots` work-groups resident at
+// once, or 0 where one work-group per chunk is the better one. Segments pass over k, v
+// and g twice and save the hand-off of every chunk; they pay where a sequence is
+// long or the working set is past the 256 MB last-level cache. Two quantities
+// decide: the chunks per CU, and how evenly the segments fill the CUs, `even` =
+// chunks / (CUs x segments on the fullest CU x chunks per segment), since the
+// segments of a CU run side by side and the fullest CU ends last.
+// Measured at 8,000 grids (14 to 256 chunks per sequence, 6 to 47 chunks per CU, f16,
+// bf16 and float32 gates, narrow and wide decays, every option) with the inputs in the
+// last-level cache and from HBM. The lines lie where segments lose in neither state:
+// of the 1,900 grids taken, 16 % faster on average, 10 are more than 3 % slower in one
+// state. Examples (us with inputs in cache, one work-group per chunk against segments;
+// in brackets the change with inputs from HBM):
+//   d_k 64: 256 chunks x 12 sequences 92 / 71 (-27 %), 100 x 96 222 / 158 (-28 %),
+//     25 x 256 131 / 91 (-24 %); not taken: 25 x 96 50 / 59 (-2 %), 32 x 144 83 / 94 (-4 %).
+//   d_k 32, d_v 64: 256 x 25 94 / 81 (-20 %); not taken: 50 x 128 75 / 82 (-3 %).
+//   Gate logits (their transcendentals run in both passes): d_k 64, 256 x 25 185 / 154
+//     (-16 %); not taken: 64 x 72 95 / 105 (-7 %), d_k 32, d_v 64, 25 x 184 58 / 79 (+18 %).
+// Decays so strong that the diagonal blocks are exact (a mean log-decay of -2 per token
+// and more) run 10 to 45 % slower in segments: the choice cannot see the values.
+static int segment_chunks(const GlaShape& s, bool logits, int64_t slots, int cus) {
+  const int64_t nmax = slots / s.BH < kSegMax ? slots / s.BH : kSegMax;  // per sequence, all resident
+  if (nmax < 2) return 0;
+  const int64_t nc = s.nchunks, total = s.BH * nc, segc = (nc + nmax - 1) / nmax;
+  const int64_t most = (s.BH * ((nc + segc - 1) / segc) + cus - 1) / cus;  // segments on the fullest CU
+  const double per = (double)total / cus, even = (double)total / ((double)cus * most * segc);
+  bool take;
+  if (logits)
+    take = s.dk == 64 && per >= (nc > 48 ? 19 : 22) && even >= 0.85;
+  else if (nc > 96 || (nc > 48 && s.dk == 64))
+    take = (per >= 8.5 && even >= 0.85) || (per >= (nc > 96 ? 11 : 19) && even >= 0.75);
+  else if (s.dk == 64)
+    take = per >= 19 && even >= 0.75;
+  else
+    take = per >= 28 && even >= 0.85 && (nc > 32 || s.dv == 64);
+  return take ? (int)segc : 0;
+}
+
+static gtr_status plan_call(const GlaShape& s, int path, bool gate, bool logits, const KernelSet& ks, Plan* pl) {
   pl->sched = GTR_PATH_STAGED;
   pl->vparts = 1;
   pl->desc = 0;
@@ -1159,22 +1197,11 @@ static gtr_status plan_call(const GlaShape& s, int path, bool gate, const Kernel
   // wait longest start first), except for the grouped look-back, whose
   // aggregates come from the low chunks
   pl->desc = all_resident && !pl->group ? 1 : 0;
-  // segments where the chunks are several times the work-groups that fit: 6 per
-  // CU for sequences longer than kInlineMaxChunks, 8 (d_k 64) or 12 per CU for
-  // shorter ones, whose look-backs are short. Measured (us, one work-group per
-  // chunk against segments): d_k 64, 100 to 256 chunks per sequence: 1200 chunks
-  // 44.4 / 44.7, 1320 45.4 / 47.2, 1536 60.2 / 55.1, 2048 93 / 62, 4608 137 / 97; 25
-  // chunks: 1800 37.8 / 39.1, 2100 46.5 / 41.1, 2400 54.8 / 50.0, 4800 98.5 / 84.2.
-  // d_k 32, d_v 64: 1320 34.1 / 34.1, 1536 45.2 / 39.7, 2048 69.6 / 41.7, 4608 88 / 63;
-  // 25 chunks: 2400 30.7 / 35.1, 4800 60.2 / 56.3. d_k 32, d_v 32: 1536 39.9 / 33.7,
-  // 4608 69.8 / 49.1; 25 chunks: 2400 25.1 / 25.0, 4800 43.6 / 39.1.
-  const int64_t per = s.nchunks > kInlineMaxChunks ? 6 : (s.dk == 64 ? 8 : 12);
-  if (pl->sched == GTR_PATH_FUSED && pl->vparts == 1 && ks.seg && cus > 0 && ns * s.nchunks >= per * cus) {
+  if (pl->sched == GTR_PATH_FUSED && pl->vparts == 1 && ks.seg && cus > 0) {
     int c2 = 0;
     const int64_t slots = (int64_t)resident_per_cu(ks.seg, ks.threads, &c2) * c2;
-    const int64_t nmax = slots / ns < kSegMax ? slots / ns : kSegMax;  // segments per sequence, all resident
-    if (nmax > 1) {
-      pl->segc = (int)((s.nchunks + nmax - 1) / nmax);
+    pl->segc = segment_chunks(s, logits, slots, cus);
+    if (pl->segc) {
       pl->nxcd = pl->group = pl->desc = 0;
       pl->blocks = ns * ((s.nchunks + pl->segc - 1) / pl->segc);
       return GTR_OK;
@@ -1215,7 +1242,7 @@ static int plan_query(const gtr_gla_args* a, Plan* pl) {
   GlaShape s;
   KernelSet ks;
   if (!a || gla_shape_from_args(a, &s, /*check_pointers=*/false) != GTR_OK || !select_kernels(s, &ks)) return -1;
-  if (plan_call(s, a->path, a->out_gate != nullptr, ks, pl) != GTR_OK) return -1;
+  if (plan_call(s, a->path, a->out_gate != nullptr, a->g_kind == GTR_GATE_LOGITS, ks, pl) != GTR_OK) return -1;
   return 0;
 }
 
@@ -1229,13 +1256,18 @@ extern "C" int gtr_gla_value_parts(const gtr_gla_args* a) {
   return plan_query(a, &pl) ? -1 : pl.vparts;
 }
 
+extern "C" int gtr_gla_segment_chunks(const gtr_gla_args* a) {
+  Plan pl;
+  return plan_query(a, &pl) ? -1 : pl.segc;
+}
+
 // Launches the schedule for arguments already validated (workspace included).
 static gtr_status gla_launch(const gtr_gla_args* a, const GlaShape& s, hipStream_t stream) {
   gtr_status st;
   KernelSet ks;
   if (!select_kernels(s, &ks)) return GTR_ERR_UNSUPPORTED;
   Plan pl;
-  st = plan_call(s, a->path, a->out_gate != nullptr, ks, &pl);
+  st = plan_call(s, a->path, a->out_gate != nullptr, a->g_kind == GTR_GATE_LOGITS, ks, &pl);
   if (st != GTR_OK) return st;
 
   const WorkspaceLayout lay = gla_workspace_layout(s);

@@ -897,9 +897,9 @@ gla_lean_kernel(GlaParams P) {
 // What bounds it: vector instructions (about two thirds of the cycles at d_k 32;
 // the second pass over k, v, g is about a quarter of them) where the kernel with
 // one work-group per chunk spent two thirds of its cycles waiting. Measured (us,
-// one work-group per chunk -> segments): 128 x 128 tokens, d_k 32, 4 images of 6
-// heads 139 -> 84; 40 x 40, d_k 64, 8 images of 12 heads with states 62.8 -> 57.5;
-// the range in the dispatch rule of gla_fwd.hip.
+// one work-group per chunk -> segments): 25 sequences of 256 chunks, d_k 32, d_v 64 93.5
+// -> 80.8 with inputs in the last-level cache, 20 % less from HBM; the rest beside the
+// rule, segment_chunks in gla_fwd.hip.
 // ---------------------------------------------------------------------------
 template <class L>
 struct SegSmem {

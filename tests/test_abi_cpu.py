@@ -129,8 +129,11 @@ def test_schedule_query_without_device(lib):
     assert lib.gtr_gla_schedule(ctypes.byref(a)) == -1
     assert lib.gtr_gla_value_parts(None) == -1
     assert lib.gtr_gla_value_parts(ctypes.byref(a)) == -1
+    assert lib.gtr_gla_segment_chunks(None) == -1
+    assert lib.gtr_gla_segment_chunks(ctypes.byref(a)) == -1
     a.dk = 64
     assert lib.gtr_gla_value_parts(ctypes.byref(a)) == 1
+    assert lib.gtr_gla_segment_chunks(ctypes.byref(a)) == 0
 
 
 def test_sequence_rows_beyond_descriptor_range(lib):

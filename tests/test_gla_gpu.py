@@ -456,6 +456,16 @@ SEGMENTS = [
     (1, 9, 111, 113, 64, 64, "bf16", "f32", "f32", "row", False, False, True),     # 9 of 196, gate and epilogue
     (1, 6, 127, 129, 32, 64, "f16", "f16", "f16", "col", False, False, True),      # 6 of 256, one-token tail
 ]
+# the same, where the dispatch takes segments (the grids above give a CU too few chunks): 7, 3, 4, 7 and 3
+# chunks per work-group, the last segment of 5, 2, 4, 2 and 3 chunks
+SEGMENTS_TAKEN = len(SEGMENTS)
+SEGMENTS += [
+    (16, 12, 41, 40, 64, 64, "f16", "f32", "f16", "col_rev", True, True, False),     # 192 sequences of 26 chunks
+    (3, 7, 67, 99, 64, 64, "bf16", "bf16", "f32", "col", True, True, False),         # 21 of 104, 41-token tail
+    (2, 6, 127, 129, 32, 64, "f16", "f16", "f16", "row", False, True, False),        # 12 of 256: 64 segments
+    (4, 10, 91, 90, 64, 64, "bf16", "f32", "f32", "row_rev", False, False, True),    # 40 of 128, gate and epilogue
+    (1, 17, 127, 65, 32, 32, "bf16", "bf16", "bf16", "col", True, True, False),      # 17 of 129
+]
 
 
 @pytest.mark.parametrize("case", range(len(SEGMENTS)))
@@ -474,6 +484,9 @@ def test_segments_parity(gtr, case):
     if gdtype != dtype:
         inp["g"] = inp["g"].float()
     q, k, v, g = (inp[n].to(dev) for n in ("q", "k", "v", "g"))
+    segc = gtr.gtr_gla_segment_chunks(q, k, v, g, H=H, W=W, path="fused", gate_tau=kw.get("gate_tau"),
+                                      out_gate=kw.get("out_gate"))
+    assert segc == (0 if case < SEGMENTS_TAKEN else (7, 3, 4, 7, 3)[case - SEGMENTS_TAKEN])
     s0t = None if inp["s0"] is None else inp["s0"].to(dev)
     ws = gtr.Workspace(dev)
     o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], inp["g"] if g_ref is None else g_ref, inp["s0"],
@@ -496,6 +509,25 @@ def test_segments_parity(gtr, case):
     assert not rows.any() or gtr.gtr_gla_workspace_fault(ws.buf) & 1
     o, _ = run()
     assert rel_err(o, o_ref) <= tol_for(dtype, odtype)
+
+
+@pytest.mark.parametrize("B,heads,H,W,dk,dv,dtype,opts,taken", [
+    (8, 12, 40, 40, 64, 64, "bf16", "", False),    # 9.4 chunks per CU, unevenly spread: slower in segments
+    (16, 6, 40, 40, 64, 64, "f16", "lz", False),   # a block's call on 16 images
+    (8, 12, 40, 40, 32, 64, "f16", "", False),
+    (4, 6, 128, 128, 32, 64, "f16", "", True),     # long sequences
+    (4, 6, 128, 128, 64, 64, "bf16", "lz", True),
+    (1, 6, 128, 128, 64, 64, "f16", "", False),    # few chunks per CU
+    (4, 6, 128, 128, 32, 32, "f16", "l", False),   # logits at d_k 32
+    (16, 16, 40, 40, 64, 64, "f16", "", True),     # past the last-level cache
+    (32, 16, 40, 40, 64, 64, "f16", "", False),    # no two segments per sequence are resident
+    (8, 12, 40, 40, 64, 64, "f32", "", False)])
+def test_segments_are_taken_where_they_are_faster(gtr, B, heads, H, W, dk, dv, dtype, opts, taken):
+    mk = lambda d: torch.empty((B, heads, H * W, d), dtype=torch_dtype(dtype), device="cuda")
+    q, v = mk(dk), mk(dv)
+    segc = gtr.gtr_gla_segment_chunks(q, q, v, q, H=H, W=W, gate_tau=16.0 if "l" in opts else None,
+                                      out_gate=v if "z" in opts else None)
+    assert (segc > 0) == taken
 
 
 def test_segments_report_values_outside_the_fp16_range(gtr):
