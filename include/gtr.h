@@ -186,7 +186,9 @@ typedef enum {
  *   bit 0  a bounded wait ran out (see spin_limit);
  *   bit 1  a bf16 q, k or v value lies outside the fp16 range (|x| > 65504):
  *          the work-groups that read it write NaN in its chunk's output rows
- *          (and, in the one-launch schedules, in everything after it).
+ *          (and, in the one-launch schedules, in everything after it; where FUSED
+ *          runs in segments, a q value does so to the end of its segment only: the
+ *          outputs and the state after it do not depend on it and are valid).
  * Read it with gtr_gla_workspace_fault after the stream has completed the call.
  *
  * Numerics: float32 accumulation throughout. With fp16/bf16 inputs the matrix

@@ -1106,6 +1106,9 @@ gla_seg_kernel(GlaParams P) {
     if (ch.lane == 0) sm.smax[ch.w] = mx;
     if (!PF) ch.template fetch<true>(P, bh, c, x);
     ch.template tokens<true, false>(P, sm, x);  // ends with a barrier
+    // A k or v outside the fp16 range is NaN in the aggregate too and poisons
+    // everything after it; a q poisons its segment from here on (the first part does
+    // not read q: with it segments take 1 to 8 % longer).
     if (ch.range_bad) {
       poison = true;
       fault |= kFaultRange;

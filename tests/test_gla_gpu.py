@@ -550,6 +550,32 @@ def test_segments_report_values_outside_the_fp16_range(gtr):
     assert rel_err(x, o_ref) <= 2e-3 and rel_err(s, sf_ref) <= 2e-3
 
 
+@pytest.mark.parametrize("name,at", [("v", 700), ("k", 6600), ("q", 700), ("q", 0), ("q", 6600)])
+def test_segments_name_what_a_value_outside_the_fp16_range_reaches(gtr, name, at):
+    """A bf16 value beyond the fp16 range in segments of 3 chunks: a k or v poisons everything from its chunk on
+    and S_final, a q the rest of its segment only (and S_final in the last one)."""
+    wl = edge_workload(3, 7, 67, 99, 64, 64, 64, "bf16", "bf16", "f32", "row", False, True, 7100)
+    inp = make_inputs(wl)
+    inp[name][1, 5, at, 3] = -1.0e6
+    dev = torch.device("cuda")
+    q, k, v, g = (inp[n].to(dev) for n in ("q", "k", "v", "g"))
+    assert gtr.gtr_gla_segment_chunks(q, k, v, g, H=wl.H, W=wl.W) == 3
+    ws = gtr.Workspace(dev)
+    o, sf = gtr.gtr_gla_fwd(q, k, v, g, H=wl.H, W=wl.W, scale=wl.scale, want_final=True, o_dtype=torch.float32,
+                            workspace=ws)
+    torch.cuda.synchronize()
+    assert gtr.gtr_gla_workspace_fault(ws.buf) == 2
+    o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], inp["g"], None, scale=wl.scale, H=wl.H, W=wl.W)
+    x, s = o.double().cpu().numpy(), sf.double().cpu().numpy()
+    lo, L = at // 64 * 64, wl.H * wl.W
+    hi = L if name != "q" else min(L, (at // 192 + 1) * 192)
+    assert np.isnan(x[1, 5, lo:hi]).all() and np.isnan(s[1, 5]).all() == (hi == L)
+    x[1, 5, lo:hi] = o_ref[1, 5, lo:hi] = 0.0
+    if hi == L:
+        s[1, 5] = sf_ref[1, 5] = 0.0
+    assert rel_err(x, o_ref) <= 2e-3 and rel_err(s, sf_ref) <= 2e-3
+
+
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("dtype,chunk", [("f16", 64), ("bf16", 32), ("f32", 64), ("f16", 128)])
 def test_gate_logits_ragged_final_state(gtr, dtype, chunk, path):
