@@ -73,6 +73,8 @@ constexpr int kFB = 2 * kFN / 8 / kFWaves;    // of W_g and W_v (2)
 constexpr int kFP = kFN / 8;             // 16-byte pieces (8 channels) of one token's kFN channels
 static_assert(kFN == 64 && kFWaves == 8 && kFH == 8 && kFW == 16, "wave and thread split");
 static_assert(kFVT * 2 % kFWaves == 0, "transfers split evenly over the waves");
+// A launch takes less than 2^32 threads: more work-groups go in several launches.
+constexpr int64_t kLaunchWgs = 0xffffffffu / (64 * kFWaves);
 
 struct GatedConvArgs {
   const void* X;
@@ -83,6 +85,7 @@ struct GatedConvArgs {
   _Float16* H;      // [B * Hh * W][hidden]
   int Hh, W, d, hidden;
   int B;            // images
+  int first, count;  // positions of the (tile, channel block) order this launch takes
 };
 
 template <int DT>
@@ -102,10 +105,9 @@ gated_conv_kernel(GatedConvArgs f) {
   const int wr = w >> 1, wc = w & 1;  // row group, channel half
   const int r16 = lane & 15, kq = lane >> 4;
   const int tiles_x = (f.W + kFW - 1) / kFW, tiles_y = (f.Hh + kFH - 1) / kFH;
-  const int tiles = f.B * tiles_x * tiles_y;
-  const int T = tiles * (f.hidden / kFN), xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int T = f.count, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int ncb = f.hidden / kFN;
-  const int j = xcd * (T >> 3) + min(xcd, T & 7) + slot;  // position in the (tile, channel block) order
+  const int j = f.first + xcd * (T >> 3) + min(xcd, T & 7) + slot;  // position in the (tile, channel block) order
   const int tile = j / ncb;
   const int tx = tile % tiles_x;
   const int ty = (tile / tiles_x) % tiles_y;
@@ -466,14 +468,18 @@ extern "C" gtr_status gtr_spatial_swiglu(const gtr_swiglu_args* a, hipStream_t s
   _Float16* Hb = reinterpret_cast<_Float16*>(ws + lay.h_off);
   const bool bf = a->dtype == GTR_BF16;
 
-  const GatedConvArgs gc{a->x, a->w_gate, a->w_value, a->conv_w, a->conv_b, Hb, a->H, a->W, a->d, a->hidden, a->B};
+  GatedConvArgs gc{a->x, a->w_gate, a->w_value, a->conv_w, a->conv_b, Hb, a->H, a->W, a->d, a->hidden, a->B, 0, 0};
   const int64_t tiles = (int64_t)a->B * ((a->H + kFH - 1) / kFH) * ((a->W + kFW - 1) / kFW);
-  const dim3 grid1((unsigned)(tiles * (a->hidden / kFN)));
-  if (bf)
-    hipLaunchKernelGGL(gated_conv_kernel<GTR_BF16>, grid1, dim3(64 * kFWaves), 0, stream, gc);
-  else
-    hipLaunchKernelGGL(gated_conv_kernel<GTR_F16>, grid1, dim3(64 * kFWaves), 0, stream, gc);
-  if (hipGetLastError() != hipSuccess) return GTR_ERR_HIP;
+  const int64_t wgs = tiles * (a->hidden / kFN);
+  for (int64_t first = 0; first < wgs; first += kLaunchWgs) {
+    gc.first = (int)first;
+    gc.count = (int)(wgs - first < kLaunchWgs ? wgs - first : kLaunchWgs);
+    if (bf)
+      hipLaunchKernelGGL(gated_conv_kernel<GTR_BF16>, dim3((unsigned)gc.count), dim3(64 * kFWaves), 0, stream, gc);
+    else
+      hipLaunchKernelGGL(gated_conv_kernel<GTR_F16>, dim3((unsigned)gc.count), dim3(64 * kFWaves), 0, stream, gc);
+    if (hipGetLastError() != hipSuccess) return GTR_ERR_HIP;
+  }
 
   const int ks = out_ksplit(M, a->d, a->hidden);
   float* part = reinterpret_cast<float*>(ws + lay.part_off);

@@ -566,28 +566,30 @@ def test_swiglu_gated_conv_addresses(dt, B, H, W, d, hidden):
     regions = [emu.Region("X", X, M * d * 2, "r"), emu.Region("Wg", WG, hidden * d * 2, "r"),
                emu.Region("Wv", WV, hidden * d * 2, "r"), emu.Region("cw", CW, hidden * 9 * 4, "r"),
                emu.Region("cb", CB, hidden * 4, "r"), emu.Region("H", HO, M * hidden * 2, "w"),
-               emu.Region("kernarg", emu.KERNARG_BASE, 64, "r")]
-    kern = struct.pack("<QQQQQQiiiii4x", X, WG, WV, CW, CB, HO, H, W, d, hidden, B)
+               emu.Region("kernarg", emu.KERNARG_BASE, 80, "r")]
     name = [n for n in emu.kernel_names(text) if "gated_conv_kernel" in n and f"ILi{dt}E" in n][0]
     with open(os.path.join(CSRC, "swiglu.hip")) as fh:
         fn = int(re.search(r"constexpr int kFN = (\d+);", fh.read()).group(1))
     tx, ty = (W + 15) // 16, (H + 7) // 8  # one work-group per 8 x 16 tokens x kFN channels
     nt, nc = B * tx * ty, hidden // fn
-    T = nt * nc
+    total = nt * nc
+    want = sorted({t * nc + c for t in (0, tx - 1, nt - 1, nt // 2) for c in (0, nc - 1)})
+    # the whole order in one launch, and its last two thirds as a launch of their own
+    for first, T in ((0, total), (total // 3, total - total // 3)):
+        kern = struct.pack("<QQQQQQiiiiiii4x", X, WG, WV, CW, CB, HO, H, W, d, hidden, B, first, T)
 
-    def block_of(tile, cb):
-        """1-D block id of (tile, channel block): XCD k = b % 8 runs positions
-        k (T // 8) + min(k, T % 8) + b // 8 of the order, channel blocks fastest."""
-        j = tile * nc + cb
-        for k in range(8):
-            start, count = k * (T // 8) + min(k, T % 8), (T - k + 7) // 8
-            if start <= j < start + count:
-                return (j - start) * 8 + k
-        raise AssertionError(j)
+        def block_of(j):
+            """1-D block id of position first + j of the (tile, channel block) order, channel blocks fastest:
+            XCD k = b % 8 runs the positions k (T // 8) + min(k, T % 8) + b // 8."""
+            for k in range(8):
+                start, count = k * (T // 8) + min(k, T % 8), (T - k + 7) // 8
+                if start <= j < start + count:
+                    return (j - start) * 8 + k
+            raise AssertionError(j)
 
-    ids = sorted({block_of(t, c) for t in (0, tx - 1, nt - 1, nt // 2) for c in (0, nc - 1)})
-    assert all(0 <= b < T for b in ids)
-    check_kernel(text, name, kern, regions, [(b, 0, 0) for b in ids], waves=8)
+        ids = sorted({block_of(j - first) for j in want if j >= first})
+        assert ids and all(0 <= b < T for b in ids)
+        check_kernel(text, name, kern, regions, [(b, 0, 0) for b in ids], waves=8)
 
 
 @pytest.mark.parametrize("cdt", [0, 1, 2])

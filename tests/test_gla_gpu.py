@@ -857,6 +857,23 @@ def test_spatial_swiglu_parity(gtr, case):
     assert rel_err(y, ref) <= tol, rel_err(y, ref)
 
 
+def test_spatial_swiglu_more_work_groups_than_one_launch_takes(gtr):
+    """2^23 + 1000 images of one token: more work-groups of 512 threads than a launch takes (2^32 threads). The
+    first and last images and those around every possible seam, against the oracle."""
+    B, d, h = (1 << 23) + 1000, 64, 64
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s, std=1.0: torch.randn(s, generator=gen, device="cuda") * std  # noqa: E731
+    x = torch.empty((B, 1, d), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    wg, wv, wo = (rnd(64, 64, std=0.125).half() for _ in range(3))
+    cw, cb = rnd(h, 3, 3, std=1 / 3), rnd(h, std=0.1)
+    y = gtr.gtr_spatial_swiglu(x, wg, wv, wo, cw, cb, H=1, W=1)
+    torch.cuda.synchronize()
+    for at in (0, (1 << 23) - 600, B - 500):
+        part = slice(at, at + 500)
+        ref = oracle.spatial_swiglu(x[part].cpu(), wg.cpu(), wv.cpu(), wo.cpu(), cw.cpu(), cb.cpu(), H=1, W=1)
+        assert rel_err(y[part], ref) <= 2e-3, at
+
+
 # ---------------------------------------------------------------------------
 # randomized shapes: a fixed-seed draw over every argument the kernels branch
 # on (sizes, head widths, chunk, dtypes, a float32 g with 16-bit inputs, scan,
