@@ -525,4 +525,200 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
   }
 }
 
+// The same product in 64 x 64 tiles with the operands staged through registers
+// (16-byte loads, four K steps in flight, written to two LDS stages a step before
+// they are multiplied), 8 waves: the waves kh = 0 and kh = 1 take the first and
+// the second 32-deep half of every step, and their sums meet through LDS at the
+// end. LN = 1 as above, the statistics taken from the pieces as they pass through
+// registers: per thread and step one piece of A and one of B, a step before the
+// MFMAs that need them, so that they run beside the waits.
+//
+// For grids of fewer tiles than CUs (see launch_gemm), where one work-group's
+// chain of K steps is the whole time and a second work-group covers no wait.
+// Measured there against the transfers straight to LDS (us, f16 / bf16): 400 x 960 x
+// 192 with LN 5.2 / 5.5 against 5.6 / 6.0, 1600 x 384 x 384 with LN 6.4 / 6.6
+// against 7.0 / 7.6, 1600 x 192 x 768 with LN 8.4 / 8.5 against 9.6 / 10.5; 1600 x 384
+// x 2304 12.5 against 13.0, operands from HBM 14.0 against 15.6; but 1600 x 384 x 384
+// 5.3 against 5.0 and 1600 x 384 x 1536 9.8 against 9.7.
+template <int ADT, int BDT, int MT, int LN>
+__global__ void __launch_bounds__(512) gemm_staged_kernel(GemmArgs g) {
+  typedef Operand<ADT, MT> OA;
+  typedef Operand<BDT, MT> OB;
+  constexpr int BM = 64, BN = 64, TI = 2, TJ = 2;  // tile; MFMA tiles per wave
+  constexpr int D = 4;                             // K steps of loads in flight
+  static_assert(BM * BN * 4 <= 2 * BM * kPitch64 * 2, "the second halves' sums fit in As");
+  __shared__ __attribute__((aligned(16))) unsigned short As[2][BM * kPitch64];
+  __shared__ __attribute__((aligned(16))) unsigned short Bs[2][BN * kPitch64];
+  __shared__ f2 lnst[LN ? BM : 1];     // per tile row: mean, 1 / sqrt(var + eps)
+  __shared__ float lncs[LN ? BN : 1];  // per tile column: the row sum of B
+
+  const int w = (threadIdx.x >> 6) & 3, kh = threadIdx.x >> 8, lane = threadIdx.x & 63;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int gx = (g.M + BM - 1) / BM, gy = g.N / BN;
+  const int T = gx * gy * g.ksplit, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int jt = xcd * (T >> 3) + min(xcd, T & 7) + slot;
+  const int by = jt % gy, bxz = jt / gy, bx = bxz % gx, bz = bxz / gx;
+  const int mb = bx * BM, nb = by * BN;
+  const int wm = (w >> 1) * (BM / 2), wn = (w & 1) * (BN / 2);
+  const int64_t K = g.K;
+  const int allsteps = g.K / 64;
+  const int s_per = (allsteps + g.ksplit - 1) / g.ksplit;
+  const int s0 = g.ksplit > 1 ? bz * s_per : 0;
+  const int s1 = min(s0 + s_per, allsteps);
+
+  // this thread's piece of each operand: row prow of the tile, 16-byte column threadIdx % 8
+  const int prow = threadIdx.x >> 3, pcol = threadIdx.x & 7;
+  const unsigned m = (unsigned)min(mb + prow, g.M - 1), at = g.a_tokens ? (unsigned)g.a_tokens : 1u;
+  const w4* ga = reinterpret_cast<const w4*>(
+      static_cast<const unsigned short*>(g.A) +
+      (g.a_tokens ? ((int64_t)(m / at) * (K / 64) * at + m % at) * 64 : (int64_t)m * K) + 8 * pcol);
+  const w4* gb = reinterpret_cast<const w4*>(static_cast<const unsigned short*>(g.B) + (int64_t)(nb + prow) * K + 8 * pcol);
+  const int64_t ast = g.a_tokens ? 8 * g.a_tokens : 8;  // 16-byte pieces from one K step of A to the next
+  const int at_lds = prow * kPitch64 + 8 * (pcol ^ kSwz64(prow));
+
+  f4 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  w4 ra[D], rb[D];
+  float sh = 0.f, sa = 0.f, sq = 0.f, sb = 0.f;  // LN: of the pieces staged so far
+  auto fetch = [&](int st, int q) {
+    ra[q] = ga[ast * st];
+    rb[q] = gb[8 * st];
+  };
+  auto stage = [&](int buf, int q) {
+    *reinterpret_cast<w4*>(&As[buf][at_lds]) = ra[q];
+    *reinterpret_cast<w4*>(&Bs[buf][at_lds]) = rb[q];
+  };
+  float one = 1.f;
+  asm volatile("" : "+v"(one));
+  auto stats = [&](int q) {
+    if constexpr (LN != 0) {
+      piece_stats<ADT>(ra[q], one, sh, sa, sq);
+      piece_sum<BDT>(rb[q], one, sb);
+    }
+  };
+  auto mma = [&](int buf) {
+    const int pc = (4 * kh + kq) ^ kSwz64(r16);
+    typename OA::T fa[TI];
+    typename OB::T fb[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+      fa[i] = OA::get(*reinterpret_cast<const w4*>(&As[buf][(wm + 16 * i + r16) * kPitch64 + 8 * pc]));
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      fb[j] = OB::get(*reinterpret_cast<const w4*>(&Bs[buf][(wn + 16 * j + r16) * kPitch64 + 8 * pc]));
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] = mfma(fb[j], fa[i], acc[i][j]);  // C^T tiles
+  };
+  // The loop runs whole groups of D steps in which every step issues the same
+  // loads (past the slice's last step they re-read that step, never used): with
+  // no load under a branch the compiler's waits count exactly, so a step waits
+  // for the loads of the step it stages, not for the newer ones. The last (steps
+  // mod D) steps follow with their loads already in flight.
+  if (s1 > s0) {
+#pragma unroll
+    for (int q = 0; q < D; ++q) fetch(min(s0 + q, s1 - 1), q);
+    if constexpr (LN != 0) sh = __shfl(first_elem<ADT>(ra[0][0]), lane & ~7, kWave);  // the row's first element
+    stage(0, 0);
+    stats(0);
+    __syncthreads();
+    int sb0 = s0;
+    for (; sb0 + D <= s1; sb0 += D) {
+#pragma unroll
+      for (int q = 0; q < D; ++q) {
+        const int st = sb0 + q, buf = (st - s0) & 1;
+        fetch(min(st + D, s1 - 1), q);  // slot q was staged before this step
+        mma(buf);
+        stage(buf ^ 1, (q + 1) % D);  // nobody reads buf ^ 1 now
+        if (st + 1 < s1) stats((q + 1) % D);  // past the last step: a re-read
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < D - 1; ++q) {
+      const int st = sb0 + q, buf = (st - s0) & 1;
+      if (st < s1) {
+        mma(buf);
+        if (st + 1 < s1) {
+          stage(buf ^ 1, (q + 1) % D);
+          stats((q + 1) % D);
+        }
+        __syncthreads();
+      }
+    }
+  }
+
+  if constexpr (LN != 0) {  // the 8 threads of a row combine; the first of each stores
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+      sa += __shfl_xor(sa, o, kWave);
+      sq += __shfl_xor(sq, o, kWave);
+      sb += __shfl_xor(sb, o, kWave);
+    }
+    if (pcol == 0) {
+      const float inv = 1.f / (float)g.K, m1 = sa * inv;
+      lnst[prow] = f2{sh + m1, rsqrtf(fmaxf(sq * inv - m1 * m1, 0.f) + g.ln_eps)};
+      lncs[prow] = sb;
+    }
+  }
+  f4* red = reinterpret_cast<f4*>(&As[0][0]) + w * TI * TJ * 64 + lane;
+  __syncthreads();  // every wave is past the K loop's last LDS read
+  if (kh == 1) {
+#pragma unroll
+    for (int q = 0; q < TI * TJ; ++q) red[64 * q] = acc[q / TJ][q % TJ];
+  }
+  __syncthreads();
+  if (kh == 1) return;
+#pragma unroll
+  for (int q = 0; q < TI * TJ; ++q) acc[q / TJ][q % TJ] += red[64 * q];
+
+  // the stores of gemm_ring_kernel
+  void* C = g.ksplit > 1 ? static_cast<void*>(g.part + (int64_t)bz * g.M * g.N) : g.C;
+  const int cdt = g.ksplit > 1 ? (int)GTR_F32 : g.cdt;
+  const bool hmc = g.ksplit == 1 && g.c_tokens != 0;
+  const unsigned tokens = hmc ? (unsigned)g.c_tokens : 1u, cdim = hmc ? (unsigned)g.c_dim : 1u;
+  const unsigned hd = hmc ? (unsigned)(g.c_heads * g.c_dim) : 1u, img = (unsigned)g.M / tokens;
+  int64_t coloff[TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const unsigned n0 = (unsigned)(nb + wn + 16 * j + 4 * kq);
+    const unsigned p = n0 / hd, r = n0 - p * hd, h = r / cdim;
+    coloff[j] = hmc ? ((int64_t)p * img * g.c_heads * tokens + (int64_t)h * tokens) * cdim + (r - h * cdim) : n0;
+  }
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    const int lr = wm + 16 * i + r16;
+    const unsigned row = (unsigned)(mb + lr);
+    if (row >= (unsigned)g.M) continue;
+    const int64_t rowoff = hmc ? ((int64_t)(row / tokens) * g.c_heads * tokens + row % tokens) * cdim : (int64_t)row * g.N;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int lc = wn + 16 * j + 4 * kq;
+      const int64_t off = rowoff + coloff[j];
+      float x[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      if constexpr (LN != 0) {
+        const f2 st = lnst[lr];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = st[1] * (x[e] - st[0] * lncs[lc + e]);
+      }
+      if (g.ksplit == 1 && g.bias) {
+        const f4 bv = *reinterpret_cast<const f4*>(g.bias + nb + lc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] += bv[e];
+      }
+      if (g.ksplit == 1 && g.res) {  // (row-major C)
+        float rv[4];
+        load4(g.res, cdt, off, rv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] += rv[e];
+      }
+      store_n<4>(C, cdt, off, x);
+    }
+  }
+}
+
 }  // namespace gtr

@@ -9,7 +9,7 @@
 //      (fp16 or bf16) and float32 accumulation, rounded to fp16 on chip, the
 //      convolution's halo recomputed per tile; H is stored in fp16, the
 //      operand type of the next product;
-//   2. gemm_ring_kernel: Y = H W_o^T (fp16 operands; bf16 weights are widened),
+//   2. gemm_ring_kernel or gemm_staged_kernel: Y = H W_o^T (fp16 operands; bf16 weights are widened),
 //      float32 partial products per K slice summed by ksplit_reduce_kernel.
 // Weights use the layout of a linear layer (output features first), so both
 // operands of every product are read along K in 16-byte pieces.
@@ -350,15 +350,18 @@ static int pick_cols(int64_t M, int N, const GemmTile& t) {
   return best;
 }
 
-// Grids of fewer than kCUs tiles leave one work-group (four waves) on a CU, and
-// its K loop is a chain of dependent steps: there the two 32-deep halves of a
-// step are summed apart (KH = 2), which cuts the chain of dependent MFMAs and of
-// float32 additions in half and rounds as the same product with its halves on
-// separate waves does. The registers are free at that size; larger grids gain
-// nothing from it.
+// Grids of fewer than kCUs 64 x 64 tiles leave one work-group on a CU, and its K
+// loop is a chain of dependent steps: there the two 32-deep halves of a step are
+// summed apart (KH = 2, or on separate waves in gemm_staged_kernel, which round
+// alike), which cuts the chain of dependent MFMAs and of float32 additions in
+// half. The registers are free at that size; larger grids gain nothing from it.
+// gemm_staged_kernel takes the row-normalised products of that size and the long
+// chains (K of kStagedK and more); the measurements are beside it.
+constexpr int kStagedK = 2048;
 template <int ADT, int BDT, int MT, bool LN>
 static void launch_gemm(GemmArgs g, hipStream_t stream) {
   const int t = g.ksplit > 1 ? 3 : pick_tile(g.M, g.N, LN);
+  const int64_t tiles = ((int64_t)g.M + 63) / 64 * (g.N / 64) * g.ksplit;  // of 64 x 64
   g.cols = LN && t < 2 ? pick_cols(g.M, g.N, kGemmTiles[t]) : 1;
   if (t == 0)
     launch_tile<ADT, BDT, MT, 128, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
@@ -366,8 +369,10 @@ static void launch_gemm(GemmArgs g, hipStream_t stream) {
     launch_tile<ADT, BDT, MT, 64, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
   else if (!LN && t == 2)
     launch_tile<ADT, BDT, MT, 64, 128, 2, 2, 2, 0>(g, stream);
-  else if (((int64_t)g.M + 63) / 64 * (g.N / 64) * g.ksplit < kCUs)
-    launch_tile<ADT, BDT, MT, 64, 64, 2, 2, LN ? 2 : 3, LN ? 1 : 0, 2>(g, stream);
+  else if (tiles < kCUs && (LN || g.K >= kStagedK))
+    hipLaunchKernelGGL((gemm_staged_kernel<ADT, BDT, MT, LN ? 1 : 0>), dim3((unsigned)tiles), dim3(512), 0, stream, g);
+  else if (!LN && tiles < kCUs)
+    launch_tile<ADT, BDT, MT, 64, 64, 2, 2, 3, 0, 2>(g, stream);
   else
     launch_tile<ADT, BDT, MT, 64, 64, 2, 2, LN ? 2 : 3, LN ? 1 : 0>(g, stream);
 }

@@ -35,7 +35,11 @@ def rnd(rng, *shape, std=1.0, dtype=torch.float16):
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("M,N,K,bias,res,cdt", [(200, 128, 192, True, True, None), (1600, 1536, 384, False, False, None),
-                                                 (37, 64, 64, True, False, torch.float32), (1, 384, 64, False, True, None)])
+                                                 (37, 64, 64, True, False, torch.float32), (1, 384, 64, False, True, None),
+                                                 # K of 2048 and more: operands staged through registers (240 and 270 tiles
+                                                 # on either side of the CUs)
+                                                 (1, 64, 2048, True, True, None), (65, 128, 2112, True, True, None),
+                                                 (2550, 384, 2304, True, True, torch.float32), (2850, 384, 2112, True, True, None)])
 def test_gemm_parity(dtype, M, N, K, bias, res, cdt):
     rng = np.random.default_rng(M + N + K)
     a, b = rnd(rng, M, K, dtype=dtype), rnd(rng, N, K, std=K ** -0.5, dtype=dtype)
@@ -69,7 +73,10 @@ def test_gemm_residual_in_place():
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("M,N,K,offset", [(1600, 1920, 384, 1.0), (200, 128, 192, 40.0), (37, 64, 64, 0.0),
-                                          (1, 384, 384, 5.0), (3200, 384, 192, 300.0)])
+                                          (1, 384, 384, 5.0), (3200, 384, 192, 300.0),
+                                          # fewer 64 x 64 tiles than CUs, one to 13 K steps (the last two 255 and 240 tiles)
+                                          (1, 64, 64, 40.0), (63, 64, 128, 40.0), (65, 192, 256, 300.0), (4100, 64, 832, 5.0),
+                                          (1088, 960, 192, 300.0), (500, 1920, 384, 40.0)])
 def test_gemm_row_norm(dtype, M, N, K, offset):
     """gtr_gemm with row_norm: the layer normalisation (no affine weights) of
     every row of a, then the product, against the float64 oracle's

@@ -503,7 +503,8 @@ def check_kernel(text, name, kern, regions, wgs, waves=4):
                                                             # rows of A normalised (the block's first layer norm)
                                                             (1, 1, 1, 64, 1600, 1920, 384, 1, 1, 16 | 8 | 1),
                                                             (2, 2, 2, 64, 37, 128, 192, 2, 1, 16 | 2),
-                                                            (1, 1, 1, 64, 200, 384, 64, 0, 1, 16)])
+                                                            (1, 1, 1, 64, 200, 384, 64, 0, 1, 16),
+                                                            (2, 2, 2, 64, 331, 960, 64, 2, 1, 16 | 8 | 1)])
 def test_swiglu_gemm_addresses(adt, bdt, mt, bn, M, N, K, cdt, ks, epi):
     """epi: bit 0 a bias, bit 1 a residual (gtr_gemm's epilogue), bits 2 / 3 head-major A / C, bit 4 the
     rows of A normalised."""
@@ -521,20 +522,22 @@ def test_swiglu_gemm_addresses(adt, bdt, mt, bn, M, N, K, cdt, ks, epi):
     ct = (M // 2 if M % 2 == 0 else M) if epi & 8 else 0
     kern = struct.pack("<QQQQiiiii4xQQqqiifi", A, B, C, P, M, N, K, cdt, ks, BI if epi & 1 else 0,
                        R if epi & 2 else 0, at, ct, 6 if ct else 0, 64 if ct else 0, 1e-6 if epi & 16 else 0.0, 0)
-    # every tile that divides N (K slices: the 64 x 64 one), each kernel of the row normalisation, and
-    # work-groups of two column tiles
+    # every tile that divides N (K slices: the 64 x 64 one), each kernel of the row normalisation,
+    # work-groups of one to three column tiles, and the kernel that stages through registers
     seen = 0
-    for bm, tn, wm, wn in ((128, 192, 2, 4), (64, 192, 2, 4), (64, 128, 2, 2), (64, 64, 2, 2)):
+    for bm, tn, wm, wn in ((128, 192, 2, 4), (64, 192, 2, 4), (64, 128, 2, 2), (64, 64, 2, 2), (64, 64, 2, 0)):
         if N % tn or (ks > 1 and tn != 64):
             continue
-        names = [n for n in emu.kernel_names(text) if "gemm_ring_kernel" in n and
-                 f"ILi{adt}ELi{bdt}ELi{mt}ELi{bm}ELi{tn}ELi{wm}ELi{wn}E" in n]
+        staged = wn == 0
+        names = [n for n in emu.kernel_names(text) if
+                 (f"gemm_staged_kernelILi{adt}ELi{bdt}ELi{mt}E" if staged else
+                  f"gemm_ring_kernelILi{adt}ELi{bdt}ELi{mt}ELi{bm}ELi{tn}ELi{wm}ELi{wn}E") in n]
         for name in names:
-            ln = int(re.search(r"ELi(\d)ELi\dEEEv", name).group(1))
+            ln = int(re.search(r"ELi(\d)EEEv" if staged else r"ELi(\d)ELi\dEEEv", name).group(1))
             if (ln > 0) != bool(epi & 16):
                 continue
             seen += 1
-            for cols in (1, 2) if ks == 1 and ln != 1 and N // tn > 1 else (1,):
+            for cols in range(1, min(3, N // tn) + 1) if ks == 1 and ln != 1 and not staged else (1,):
                 gx, gy = (M + bm - 1) // bm, (N // tn + cols - 1) // cols
                 T = gx * gy * ks
 
@@ -552,7 +555,7 @@ def test_swiglu_gemm_addresses(adt, bdt, mt, bn, M, N, K, cdt, ks, epi):
                               for z in sorted({0, ks - 1})})
                 assert all(0 <= b < T for b in ids)
                 check_kernel(text, name, kern[:-4] + struct.pack("<i", cols), regions, [(b, 0, 0) for b in ids],
-                             waves=wm * wn)
+                             waves=8 if staged else wm * wn)
     assert seen > 0
 
 
