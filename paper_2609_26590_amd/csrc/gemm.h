@@ -248,8 +248,11 @@ __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, i
 // x 384 in 128 x 128 tiles 68 us with three, which leave room for one work-group,
 // 39 with two); three for 64 x 64, whose grids are small and whose operands come
 // from beyond the L2 (1600 x 384 x 1536 over rotating weights 13.8 us with two,
-// 10.4 with three, 10.6 with four). Measured (us, operands staged through
-// registers -> now, rotating operands): 12800 x 1920 x 384 with LN 68 -> 43, 8300 x
+// 10.4 with three, 10.6 with four); three for 64 x 128 where each CU has one
+// work-group (two against three, operands from HBM: 4150 x 384 x 1536 21.7 against
+// 15.1, 1600 x 768 x 3072 39 against 25; from cache 13.2 against 13.7, 27.8 against
+// 23.2). Measured (us, operands staged through registers -> straight to LDS, rotating
+// operands): 12800 x 1920 x 384 with LN 68 -> 43, 8300 x
 // 1920 x 384 with LN 47 -> 35, 12800 x 384 x 1536 34.1 -> 27.5, 12800 x 384 x 384
 // 15.9 -> 12.6, 1600 x 1920 x 384 with LN 13.1 -> 11.3, 1600 x 384 x 384 6.0 -> 5.5,
 // 1600 x 384 x 1536 10.4 -> 10.4.

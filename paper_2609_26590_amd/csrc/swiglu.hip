@@ -367,6 +367,8 @@ static void launch_gemm(GemmArgs g, hipStream_t stream) {
     launch_tile<ADT, BDT, MT, 128, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
   else if (t == 1)
     launch_tile<ADT, BDT, MT, 64, 192, 2, 4, 2, LN ? 2 : 0>(g, stream);
+  else if (!LN && t == 2 && tiles <= 2 * kCUs)  // one work-group per CU: a third stage covers the wait
+    launch_tile<ADT, BDT, MT, 64, 128, 2, 2, 3, 0>(g, stream);
   else if (!LN && t == 2)
     launch_tile<ADT, BDT, MT, 64, 128, 2, 2, 2, 0>(g, stream);
   else if (tiles < kCUs && (LN || g.K >= kStagedK))

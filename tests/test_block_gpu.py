@@ -102,7 +102,8 @@ def test_gemm_row_norm(dtype, M, N, K, offset):
 @pytest.mark.parametrize("norm", [False, True])
 @pytest.mark.parametrize("M,N,K", [(1, 192, 64), (65, 384, 128), (63, 128, 192),        # one row, one to three K steps
                                    (4097, 1920, 192), (12801, 1920, 64), (3300, 960, 192),  # 128- and 64-row tiles of 192
-                                   (8300, 384, 448), (16390, 128, 64), (20000, 64, 128)])  # 128- and 64-column tiles
+                                   (8300, 384, 448), (16390, 128, 64), (20000, 64, 128),  # 128- and 64-column tiles
+                                   (4150, 384, 64), (4100, 384, 128), (4120, 384, 320)])  # 195 tiles of 128 columns
 def test_gemm_tiles(dtype, norm, M, N, K):
     """gtr_gemm at row counts that no tile divides, over every tile of the
     dispatch, with one to seven K steps, against a float64 product (and layer
