@@ -412,7 +412,7 @@ static gtr_status swiglu_check(const gtr_swiglu_args* a, int64_t* M_out, bool ch
   int64_t L, M, n;
   if (__builtin_mul_overflow((int64_t)a->H, (int64_t)a->W, &L) || __builtin_mul_overflow(L, (int64_t)a->B, &M))
     return GTR_ERR_SHAPE;
-  if (M > 0x7fffffff - 64 || __builtin_mul_overflow(M, (int64_t)a->hidden, &n) || n > ((int64_t)1 << 40))
+  if (M > 0x7fffffff - 128 || __builtin_mul_overflow(M, (int64_t)a->hidden, &n) || n > ((int64_t)1 << 40))
     return GTR_ERR_SHAPE;
   // both launches number their work-groups with 32-bit ints
   const int64_t tiles = (int64_t)a->B * ((a->H + kFH - 1) / kFH) * ((a->W + kFW - 1) / kFW);

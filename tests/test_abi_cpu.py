@@ -136,6 +136,16 @@ def test_schedule_query_without_device(lib):
     assert lib.gtr_gla_segment_chunks(ctypes.byref(a)) == 0
 
 
+def test_swiglu_rows_fit_the_largest_tile(lib):
+    """The products round the row count up to tiles of 128 rows in 32-bit integers."""
+    a = gtr.SwigluArgs()
+    a.dtype = a.y_dtype = gtr.F16
+    a.B, a.H, a.d, a.hidden = 1, 1, 64, 64
+    for rows, ok in ((2 ** 31 - 1 - 128, True), (2 ** 31 - 128, False), (2 ** 31 - 65, False)):
+        a.W = rows
+        assert (lib.gtr_spatial_swiglu_workspace_size(ctypes.byref(a)) > 0) == ok, rows
+
+
 def test_sequence_rows_beyond_descriptor_range(lib):
     """One sequence's rows are addressed through a 32-bit buffer descriptor:
     L * max(dk, dv) * 4 bytes must stay below 0x7fffff00."""
