@@ -87,7 +87,10 @@ __device__ __forceinline__ void load4(const void* base, int dt, int64_t off, flo
 // Memory straight to LDS: lane l's 16 bytes at g go to LDS byte lds + 16 l (lds
 // wave-uniform). The instruction writes no register, so nothing the compiler
 // tracks is in flight; it does not know of the transfer either, and every use
-// of the data is behind ring_wait.
+// of the data is behind ring_wait. M0, which holds the LDS address, is reserved:
+// the compiler allocates nothing to it and warns when it is named as clobbered, so
+// a kernel with these transfers must hold no other instruction that reads M0 (the
+// tests check the listing for one).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void dma16(const void* g, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");

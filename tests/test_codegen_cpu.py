@@ -474,6 +474,26 @@ def swiglu_asm() -> str:
         return fh.read()
 
 
+def test_nothing_but_the_transfers_uses_m0():
+    """The transfers to LDS set M0 without the compiler's knowledge: in a kernel that has them, M0 appears
+    only as their LDS address, set right before each, and no instruction that reads it implicitly appears."""
+    text = swiglu_asm()
+    found = 0
+    for name in emu.kernel_names(text):
+        body = text[text.index(f"\n{name}:"):]
+        body = body[:body.index(".Lfunc_end")]
+        lines = [x for x in (ln.split(";")[0].strip() for ln in body.split("\n")) if x and not x.startswith(".")]
+        moves = [i for i, ln in enumerate(lines) if "global_load_lds" in ln]
+        found += bool(moves)
+        for i in moves:
+            assert re.match(r"s_mov_b32 m0, s\d+$", lines[i - 2]) and lines[i - 1] == "s_nop 0", lines[i - 2:i + 1]
+        if moves:
+            assert sum("m0" in ln for ln in lines) == len(moves), name
+            implicit = re.compile(r"(v_movrel|s_movrel|v_interp|s_sendmsg|ds_gws|ds_\w*addtid|ds_ordered|buffer_load\S* .*\blds\b)")
+            assert not [ln for ln in lines if implicit.match(ln)], name
+    assert found >= 10
+
+
 def check_kernel(text, name, kern, regions, wgs, waves=4):
     prog, labels, desc = emu.parse_kernel(text, name)
     rep = emu.Report()
