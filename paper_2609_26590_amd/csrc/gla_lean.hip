@@ -72,6 +72,11 @@ struct Lean {
   static constexpr int kFk = 1;    // 2^(sum of the totals after R): summary
   static constexpr int kFh = 2;    // 2^(-T_R / 2): diagonal mid-point
   static constexpr int kFoff = 3;  // + J: 2^(sum of the totals between J and R), J < R
+  // The lane's token is kept from the loads to the stores, except at d_k = d_v = 64:
+  // there a register over the whole kernel is one too many (the segment kernel spills
+  // it), and formed anew at the stores it costs bf16 0.5 % and saves f16 1 to 3 %. At
+  // d_k = 32 keeping it saves up to 8 % (column scans, two divisions per token).
+  static constexpr bool kKeep = !(DK == 64 && DV == 64);
   // spans of the diagonal tiers in base-2 units
   static constexpr float kSpanF16b = kSpanF16 * kLog2e, kSpanF32b = kSpanF32 * kLog2e;
 
@@ -95,6 +100,8 @@ struct Lean {
   };
 
   int w, lane, tr, g, r;
+  unsigned tok;      // kKeep: spatial index of this lane's token (0 past the end of the sequence)
+  bool tok_ok;       // kKeep: the position exists
   float qh[KS][8];   // q 2^(a_r)
   float ke[KS][8];   // k 2^(T_R - a_r)
   h8 qt[KS];         // q 2^(A_r), the readout operand
@@ -125,6 +132,14 @@ struct Lean {
   static __device__ __forceinline__ unsigned token(const GlaParams& P, unsigned pos, bool& valid) {
     valid = pos < (unsigned)P.L;
     return valid ? scan_token(P, pos) : 0u;
+  }
+  // This lane's token of chunk c: kept from the loads, or formed anew.
+  __device__ __forceinline__ unsigned my_token(const GlaParams& P, int c, bool& valid) const {
+    if constexpr (kKeep) {
+      valid = tok_ok;
+      return tok;
+    }
+    return token(P, (unsigned)(c * C) + r, valid);
   }
 
   // The lane's place as values the compiler does not know: inside a loop over
@@ -189,6 +204,7 @@ struct Lean {
   template <bool WITHQ, bool SCALES, class S>
   __device__ __forceinline__ void tokens(const GlaParams& P, S& sm, const Rows& x) {
     const bool valid = x.ok;
+    if constexpr (kKeep) tok = x.tok, tok_ok = x.ok;
     // log2-decays and their inclusive sums within the sub-chunk
     float a[KS][8], tot[KS][8];
     float spn = 0.f, am = 0.f, vm = 0.f;
@@ -258,7 +274,7 @@ struct Lean {
     }
     range_bad = false;
     if constexpr (SCALES) {
-      am = WITHQ ? absmax : wave_max_uniform(am);
+      am = WITHQ && !S::kBallot ? absmax : wave_max_uniform(am);
       vm = wave_max_uniform(vm);
       if (lane == 0) {
         sm.M[w][0] = am;
@@ -381,7 +397,7 @@ struct Lean {
   // the raw q, k, g of the sub-chunk (reloaded; rare).
   __device__ __forceinline__ f4 exact_diagonal(const GlaParams& P, float (*pt)[17], int bh, int c) const {
     bool valid;
-    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
+    const unsigned t = my_token(P, c, valid);
     const int64_t kb = ((int64_t)bh * P.L + t) * DK;
     float qx[KS][8], kx[KS][8], ax[KS][8];
 #pragma unroll
@@ -610,7 +626,7 @@ struct Lean {
   // early, with the other inputs; only when P.gate is set).
   __device__ __forceinline__ void prefetch_gate(const GlaParams& P, int bh, int c, Raw (&rz)[VB]) const {
     bool valid;
-    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
+    const unsigned t = my_token(P, c, valid);
 #pragma unroll
     for (int jb = 0; jb < VB; ++jb) {
       const int64_t off = ((int64_t)bh * P.L + t) * P.dvp + 16 * jb + 4 * g;
@@ -629,7 +645,7 @@ struct Lean {
   __device__ __forceinline__ void store(const GlaParams& P, int bh, int c, const f4 (&O)[VB], const Raw (&rz)[VB],
                                         bool poison) const {
     bool valid;
-    const unsigned t = token(P, (unsigned)(c * C) + r, valid);
+    const unsigned t = my_token(P, c, valid);
     const float mul = poison ? __builtin_nanf("") : P.scale;
     float x[VB][4];
 #pragma unroll
