@@ -1109,10 +1109,15 @@ constexpr int64_t kSegMax = 64;  // segments per sequence: one ballot of their f
 // decide: the chunks per CU, and how evenly the segments fill the CUs, `even` =
 // chunks / (CUs x segments on the fullest CU x chunks per segment), since the
 // segments of a CU run side by side and the fullest CU ends last.
-// Measured at 8,000 grids (14 to 256 chunks per sequence, 6 to 47 chunks per CU, f16,
+// For sequences of more than 96 chunks the number of sequences is a third one: in the
+// chunk-major grid of one work-group per chunk, work-group b on XCD b mod 8, the chunks
+// of a sequence run on 8 / gcd(8, sequences) XCDs, and the fewer those are the longer
+// the look-back takes (d_k 64, ns per chunk with 7, 8, 9 sequences of 196 to 256 chunks 33,
+// 42, 31, with 11, 12 28, 32); segments do not mind (35, 30, 30, 29, 25).
+// Measured at 5,900 grids (14 to 256 chunks per sequence, 6 to 47 chunks per CU, f16,
 // bf16 and float32 gates, narrow and wide decays, every option) with the inputs in the
 // last-level cache and from HBM. The lines lie where segments lose in neither state:
-// of the 1,900 grids taken, 16 % faster on average, 10 are more than 3 % slower in one
+// the 2,540 grids taken are 20 % faster on average, 8 are 4 to 6 % slower in one
 // state. Examples (us with inputs in cache, one work-group per chunk against segments;
 // in brackets the change with inputs from HBM):
 //   d_k 64: 256 chunks x 12 sequences 92 / 71 (-27 %), 100 x 96 222 / 158 (-28 %),
@@ -1128,9 +1133,16 @@ static int segment_chunks(const GlaShape& s, bool logits, int64_t slots, int cus
   const int64_t nc = s.nchunks, total = s.BH * nc, segc = (nc + nmax - 1) / nmax;
   const int64_t most = (s.BH * ((nc + segc - 1) / segc) + cus - 1) / cus;  // segments on the fullest CU
   const double per = (double)total / cus, even = (double)total / ((double)cus * most * segc);
+  const bool one_xcd = nc > 96 && s.BH % 8 == 0;
   bool take;
-  if (logits)
+  if (one_xcd && !logits)
+    take = per >= 6;
+  else if (one_xcd && per >= 13 && even >= (s.dv == 64 ? 0.85 : 0.93))
+    take = true;
+  else if (logits)
     take = s.dk == 64 && per >= (nc > 48 ? 19 : 22) && even >= 0.85;
+  else if (nc > 96 && s.dk == 64 && s.BH % 2)  // on all eight XCDs: the fastest look-back
+    take = per >= 16 && even >= 0.75;
   else if (nc > 96 || (nc > 48 && s.dk == 64))
     take = (per >= 8.5 && even >= 0.85) || (per >= (nc > 96 ? 11 : 19) && even >= 0.75);
   else if (s.dk == 64)

@@ -456,12 +456,12 @@ SEGMENTS = [
     (1, 9, 111, 113, 64, 64, "bf16", "f32", "f32", "row", False, False, True),     # 9 of 196, gate and epilogue
     (1, 6, 127, 129, 32, 64, "f16", "f16", "f16", "col", False, False, True),      # 6 of 256, one-token tail
 ]
-# the same, where the dispatch takes segments (the grids above give a CU too few chunks): 7, 3, 4, 7 and 3
-# chunks per work-group, the last segment of 5, 2, 4, 2 and 3 chunks
-SEGMENTS_TAKEN = len(SEGMENTS)
+# the same, where the dispatch takes segments (most grids above give a CU too few chunks); the last segment
+# has 5, 2, 4, 2 and 3 chunks
+SEGMENTS_CHUNKS = (0, 3, 0, 0, 0, 7, 3, 4, 7, 3)  # chunks per work-group, 0: one
 SEGMENTS += [
     (16, 12, 41, 40, 64, 64, "f16", "f32", "f16", "col_rev", True, True, False),     # 192 sequences of 26 chunks
-    (3, 7, 67, 99, 64, 64, "bf16", "bf16", "f32", "col", True, True, False),         # 21 of 104, 41-token tail
+    (2, 8, 67, 99, 64, 64, "bf16", "bf16", "f32", "col", True, True, False),         # 16 of 104, 41-token tail
     (2, 6, 127, 129, 32, 64, "f16", "f16", "f16", "row", False, True, False),        # 12 of 256: 64 segments
     (4, 10, 91, 90, 64, 64, "bf16", "f32", "f32", "row_rev", False, False, True),    # 40 of 128, gate and epilogue
     (1, 17, 127, 65, 32, 32, "bf16", "bf16", "bf16", "col", True, True, False),      # 17 of 129
@@ -486,7 +486,7 @@ def test_segments_parity(gtr, case):
     q, k, v, g = (inp[n].to(dev) for n in ("q", "k", "v", "g"))
     segc = gtr.gtr_gla_segment_chunks(q, k, v, g, H=H, W=W, path="fused", gate_tau=kw.get("gate_tau"),
                                       out_gate=kw.get("out_gate"))
-    assert segc == (0 if case < SEGMENTS_TAKEN else (7, 3, 4, 7, 3)[case - SEGMENTS_TAKEN])
+    assert segc == SEGMENTS_CHUNKS[case]
     s0t = None if inp["s0"] is None else inp["s0"].to(dev)
     ws = gtr.Workspace(dev)
     o_ref, sf_ref = oracle.gla(inp["q"], inp["k"], inp["v"], inp["g"] if g_ref is None else g_ref, inp["s0"],
@@ -519,6 +519,13 @@ def test_segments_parity(gtr, case):
     (4, 6, 128, 128, 64, 64, "bf16", "lz", True),
     (1, 6, 128, 128, 64, 64, "f16", "", False),    # few chunks per CU
     (4, 6, 128, 128, 32, 32, "f16", "l", False),   # logits at d_k 32
+    (4, 6, 128, 128, 32, 64, "f16", "lz", True),   # the same, every sequence on one XCD
+    (5, 5, 128, 128, 32, 64, "f16", "l", False),
+    (1, 8, 128, 128, 32, 64, "bf16", "", True),    # on one XCD: from 6 chunks per CU on
+    (1, 7, 128, 128, 32, 64, "bf16", "", False),
+    (1, 13, 128, 128, 64, 64, "bf16", "", False),  # odd: on all XCDs, 13 and 17 chunks per CU
+    (1, 17, 128, 128, 64, 64, "bf16", "", True),
+    (1, 12, 128, 128, 64, 64, "bf16", "", True),   # on two
     (16, 16, 40, 40, 64, 64, "f16", "", True),     # past the last-level cache
     (32, 16, 40, 40, 64, 64, "f16", "", False),    # no two segments per sequence are resident
     (8, 12, 40, 40, 64, 64, "f32", "", False)])
@@ -554,7 +561,7 @@ def test_segments_report_values_outside_the_fp16_range(gtr):
 def test_segments_name_what_a_value_outside_the_fp16_range_reaches(gtr, name, at):
     """A bf16 value beyond the fp16 range in segments of 3 chunks: a k or v poisons everything from its chunk on
     and S_final, a q the rest of its segment only (and S_final in the last one)."""
-    wl = edge_workload(3, 7, 67, 99, 64, 64, 64, "bf16", "bf16", "f32", "row", False, True, 7100)
+    wl = edge_workload(2, 8, 67, 99, 64, 64, 64, "bf16", "bf16", "f32", "row", False, True, 7100)
     inp = make_inputs(wl)
     inp[name][1, 5, at, 3] = -1.0e6
     dev = torch.device("cuda")
