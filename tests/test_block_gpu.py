@@ -76,13 +76,19 @@ def test_gemm_residual_in_place():
                                           (1, 384, 384, 5.0), (3200, 384, 192, 300.0),
                                           # fewer 64 x 64 tiles than CUs, one to 13 K steps (the last two 255 and 240 tiles)
                                           (1, 64, 64, 40.0), (63, 64, 128, 40.0), (65, 192, 256, 300.0), (4100, 64, 832, 5.0),
-                                          (1088, 960, 192, 300.0), (500, 1920, 384, 40.0)])
+                                          (1088, 960, 192, 300.0), (500, 1920, 384, 40.0),
+                                          # 64 x 192 and 128 x 192 tiles, one column tile per work-group, then
+                                          # groups of two of ten and, the last group short, three of five
+                                          (1600, 1920, 384, 300.0), (12801, 1920, 64, 300.0), (15300, 960, 64, 40.0),
+                                          (30500, 960, 64, 5.0)])
 def test_gemm_row_norm(dtype, M, N, K, offset):
     """gtr_gemm with row_norm: the layer normalisation (no affine weights) of
     every row of a, then the product, against the float64 oracle's
     layer_norm. Row means up to 300 times the spread check the shifted
     squares; every seventh row is constant (variance zero, the result is the
-    bias alone); grids below and above 256 tiles run both kernel shapes."""
+    bias alone). Grids below 256 tiles take the statistics from the pieces on
+    their way through registers, 64 x 64 tiles above that from the operands, the
+    wide tiles from a pass over the rows before the products."""
     rng = np.random.default_rng(M + K)
     a = (rnd(rng, M, K, dtype=torch.float32) * 3 + torch.from_numpy(rng.uniform(-1, 1, (M, 1)) * offset).float())
     a[::7] = torch.from_numpy(rng.uniform(-4, 4, (len(range(0, M, 7)), 1))).float()  # constant rows: zero spread
@@ -101,8 +107,9 @@ def test_gemm_row_norm(dtype, M, N, K, offset):
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("norm", [False, True])
 @pytest.mark.parametrize("M,N,K", [(1, 192, 64), (65, 384, 128), (63, 128, 192),        # one row, one to three K steps
-                                   (4097, 1920, 192), (12801, 1920, 64), (3300, 960, 192),  # 128- and 64-row tiles of 192
-                                   (8300, 384, 448), (16390, 128, 64), (20000, 64, 128),  # 128- and 64-column tiles
+                                   (12801, 1920, 64), (1600, 1920, 192), (5000, 576, 64),  # 128 x 192, 64 x 192 twice,
+                                   (4097, 1920, 192), (8300, 384, 448),                   # 64 x 128 (norm: 64 x 192, 64 x 64),
+                                   (3300, 960, 192), (16390, 128, 64), (20000, 64, 128),  # 64 x 64
                                    (4150, 384, 64), (4100, 384, 128), (4120, 384, 320)])  # 195 tiles of 128 columns
 def test_gemm_tiles(dtype, norm, M, N, K):
     """gtr_gemm at row counts that no tile divides, over every tile of the
