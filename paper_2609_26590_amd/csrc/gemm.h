@@ -49,22 +49,6 @@ __device__ __forceinline__ f4 mfma(const bf8& a, const bf8& b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// 8 consecutive 16-bit elements of dtype DT (one 16-byte piece) as floats.
-template <int DT>
-__device__ __forceinline__ void unpack_piece(const w4& v, float (&x)[8]) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const unsigned u = v[e];
-    if (DT == GTR_F16) {
-      x[2 * e] = (float)__builtin_bit_cast(_Float16, (unsigned short)(u & 0xffffu));
-      x[2 * e + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(u >> 16));
-    } else {
-      x[2 * e] = __builtin_bit_cast(float, u << 16);
-      x[2 * e + 1] = __builtin_bit_cast(float, u & 0xffff0000u);
-    }
-  }
-}
-
 // 4 consecutive elements of dtype dt at element offset off, as floats.
 __device__ __forceinline__ void load4(const void* base, int dt, int64_t off, float (&x)[4]) {
   if (dt == GTR_F32) {
@@ -135,7 +119,7 @@ struct GemmArgs {
                       // m % a_tokens), K step s = head s (a head concat read in place)
   int64_t c_tokens;   // C is written [N / (c_heads c_dim)][M / c_tokens][c_heads][c_tokens][c_dim]
   int c_heads, c_dim;
-  float ln_eps;       // the row normalisation's epsilon (kernels with LN = 1)
+  float ln_eps;       // the row normalisation's epsilon (kernels with LN != 0)
   int cols;           // column tiles a work-group takes one after the other
 };
 
@@ -186,8 +170,9 @@ __device__ __forceinline__ float first_elem(unsigned u) {
 
 // Mean and 1 / sqrt(var + eps) of the BM rows of A from row mb on, over K
 // columns, into st: 8 lanes per row (lane l takes pieces l, l + 8, .., the order of
-// LN = 1's sums), BM / NW rows per wave, from memory (the rows the ring reads next). Squares are taken about the row's first element,
-// so that a mean large next to the spread costs no precision.
+// LN = 1's sums), BM / NW rows per wave, from memory (the rows the ring reads
+// next). Squares are taken about the row's first element, so that a mean large
+// next to the spread costs no precision.
 template <int ADT, int BM, int NW>
 __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, int lane, f2* st) {
   constexpr int RW = BM / NW, G = RW % 16 == 0 ? 2 : 1, U = 6;  // rows per wave; groups of 8 rows, pieces in flight
@@ -254,11 +239,11 @@ __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, i
 // 10.4 with three, 10.6 with four); three for 64 x 128 where each CU has one
 // work-group (two against three, operands from HBM: 4150 x 384 x 1536 21.7 against
 // 15.1, 1600 x 768 x 3072 39 against 25; from cache 13.2 against 13.7, 27.8 against
-// 23.2). Measured (us, operands staged through registers -> straight to LDS, rotating
-// operands): 12800 x 1920 x 384 with LN 68 -> 43, 8300 x
-// 1920 x 384 with LN 47 -> 35, 12800 x 384 x 1536 34.1 -> 27.5, 12800 x 384 x 384
-// 15.9 -> 12.6, 1600 x 1920 x 384 with LN 13.1 -> 11.3, 1600 x 384 x 384 6.0 -> 5.5,
-// 1600 x 384 x 1536 10.4 -> 10.4.
+// 23.2). Measured (us, operands staged through registers -> straight to LDS, operands
+// from HBM): 12800 x 1920 x 384 with LN 62.7 -> 39.9, 8300 x 1920 x 384 with LN
+// 43.4 -> 33.9, 12800 x 384 x 1536 37.2 -> 31.4, 12800 x 384 x 384 16.8 -> 13.3,
+// 1600 x 1920 x 384 with LN 12.3 -> 10.6, 1600 x 384 x 384 5.6 -> 5.0; 1600 x 384 x
+// 1536 10.3 -> 10.4.
 //
 // A work-group takes `cols` column tiles of its row block one after the other
 // (one transfer chain across them), so that the row statistics of LN = 2 are
@@ -272,11 +257,16 @@ __device__ __forceinline__ void row_stats(const GemmArgs& g, int mb, int wave, i
 // The row sums and the statistics are taken in one fixed order for every tile (8
 // lanes per row, pieces l, l + 8, ..), so that a product rounds alike in all of
 // them; an MFMA against ones for the sums would take 0.5 us less at 1600 x 1920 x
-// 384 and round another way. KH: see launch_gemm.
+// 384 and round another way.
 // The statistics come from the operands as they are read (LN = 1: no extra
 // load, for small tiles and short chains) or from a pass over the rows before
 // the loop (LN = 2: no extra registers in the loop, for the larger tiles).
-// Both need K in one slice and a row-major A, LN = 1 also cols = 1.
+// Both need K in one slice and a row-major A, LN = 1 also cols = 1. (In 128 x 192
+// tiles LN = 2 spills two registers, stored once before the products and loaded
+// once in the epilogue of a tile.)
+//
+// KH = 2 sums the two 32-deep halves of every step apart (grids of fewer 64 x 64
+// tiles than CUs).
 //
 // The grid is one-dimensional. Work-group b runs on XCD b % 8 (round-robin
 // dispatch), and each XCD takes a contiguous range of the order (slice, row
@@ -292,7 +282,7 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
   constexpr int PA = BM / 8 / NW, PB = BN / 8 / NW;      // transfers per wave per step
   constexpr int PL = PA + PB;
   constexpr int SA = BM * kPitch64, SB = BN * kPitch64;  // elements per stage
-  static_assert(S >= 2 && S <= 4, "stages");
+  static_assert(S == 2 || S == 3, "stages");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tiles split evenly over the waves");
   __shared__ __attribute__((aligned(1024))) unsigned short ring[S * (SA + SB)];
   __shared__ f2 lnp[LN == 1 ? WN : 1][LN == 1 ? BM : 1];  // LN = 1: per tile row, the waves' sums and squares
@@ -421,9 +411,7 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 4 : 2))) gemm_ring_kernel(Gemm
       // this step's stage has landed (the stages after it may be in flight), and
       // every wave is done with the one before it, which the next transfer fills
       const int rem = total - 1 - f;  // steps after this one
-      if (S == 4 && rem >= 2)
-        ring_wait<2 * PL>();
-      else if (S >= 3 && rem >= 1)
+      if (S == 3 && rem >= 1)
         ring_wait<PL>();
       else
         ring_wait<0>();

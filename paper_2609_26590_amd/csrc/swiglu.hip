@@ -293,17 +293,20 @@ gated_conv_kernel(GatedConvArgs f) {
 }
 
 // ---------------------------------------------------------------------------
-// Tile of a product (gemm_ring_kernel). The CUs run in lockstep through
-// ceil(tiles / CUs) tiles each, so the time goes with that count times the
-// tile's area; per area a larger tile is faster, as it reads fewer operand
-// bytes per product. Measured per area against 128 x 192 (us at 12800 x 384 x
-// 2304: 128 x 192 36, 64 x 192 39, 64 x 128 39, 64 x 64 45; 12800 x 1920 x 384: 36,
-// 43, 43, 46): the weights below. Where the larger tile leaves CUs idle the
+// Tile of a product. The CUs run in lockstep through ceil(tiles / CUs) tiles
+// each, so the time goes with that count times the tile's area; per area a larger
+// tile is faster, as it reads fewer operand bytes per product: at 12800 x 384 x
+// 2304 64 x 192, 64 x 128 and 64 x 64 take 1.08, 1.08 and 1.25 times as long as 128 x
+// 192 (36 us), at 12800 x 1920 x 384 1.19, 1.19 and 1.28 times (36 us). The weights
+// below lie between. Where the larger tile leaves CUs idle the
 // smaller one wins, as the rule says: 8300 x 384 x 1536 20.1 in 64 x 128 (390
 // tiles) against 25.3 in 128 x 192 (130); 1600 x 384 x 1536 9.7 in 64 x 64 (150)
 // against 14.2 in 64 x 128 (75); with LN 1600 x 1920 x 384 10.6 in 64 x 192 (250)
 // against 11.4 in 64 x 64 (750), 1600 x 960 x 192 6.9 in 64 x 64 (375) against 8.0 in
-// 64 x 192 (125). All widths that no wider tile divides run in 64 x 64.
+// 64 x 192 (125). All widths that no wider tile divides run in 64 x 64. Known
+// misses: 3200 to 5000 x 384 x 1536 and 2304 with inputs from cache, 64 x 64 up to 14 %
+// faster than the 64 x 128 taken (from HBM 8 % slower); from 20000 rows on, 128 x 192
+// up to 12 % faster than 64 x 192; 10000 x 1920 x 384 with LN 42.5 against 38.4.
 // ---------------------------------------------------------------------------
 constexpr int kCUs = 256;
 constexpr int kGemmBM = 64, kGemmBN = 64;  // the smallest tile
@@ -336,8 +339,9 @@ static void launch_tile(const GemmArgs& g, hipStream_t stream) {
 // Column tiles per work-group of the row-normalised product in wide tiles: the
 // statistics of a row block cost about half a tile, once per work-group, and
 // two work-groups share a CU, so the time goes with max(1, work-groups / (2
-// CUs)) (cols + 1/2). Measured (us): 12800 x 1920 x 384 47 with one column tile,
-// 43.5 with two (500 work-groups), 51 with three; 8300 x 1920 x 384 35.4, 36.7, 46.
+// CUs)) (cols + 1/2). Measured (us with one, two and three column tiles): 12800 x
+// 1920 x 384 44.0, 40.4 (500 work-groups), 52.5; 8300 x 1920 x 384 31.7, 36.3, 48.0;
+// 30500 x 1920 x 384 113, 104, 115; 15300 x 960 x 384 24.8, 25.4, 24.6 (takes three).
 static int pick_cols(int64_t M, int N, const GemmTile& t) {
   const int64_t rows = (M + t.bm - 1) / t.bm, ntile = N / t.bn;
   int best = 1;
@@ -505,8 +509,7 @@ extern "C" gtr_status gtr_spatial_swiglu(const gtr_swiglu_args* a, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// gtr_gemm: C = A B^T (+ bias) (+ res) on gemm_ring_kernel, 64 x 64 tiles, no
-// K split (the block's products have K = d or 64).
+// gtr_gemm: C = A B^T (+ bias) (+ res) through launch_gemm, K in one slice.
 // ---------------------------------------------------------------------------
 static gtr_status gemm_check(const gtr_gemm_args* a) {
   if (a->M <= 0 || a->N <= 0 || a->K <= 0 || a->a_tokens < 0 || a->c_tokens < 0) return GTR_ERR_SHAPE;
