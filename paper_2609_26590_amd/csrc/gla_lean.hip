@@ -912,10 +912,9 @@ gla_lean_kernel(GlaParams P) {
 // up to 22 of them back, round after round of work-groups.
 // What bounds it: no one unit. At 24 sequences of 256 chunks, d_k 32, d_v 64, three
 // waves per SIMD, vector instructions take 47 % of the SIMDs' cycles and MFMAs 5 %,
-// and the waves wait half of their time; the second pass over k, v, g is about a
-// quarter of the vector instructions. Measured (us,
-// one work-group per chunk -> segments): 25 sequences of 256 chunks, d_k 32, d_v 64 93.5
-// -> 80.8 with inputs in the last-level cache, 20 % less from HBM; the rest beside the
+// and the waves wait half of their time. Measured (us, one work-group per chunk ->
+// segments): 25 sequences of 256 chunks, d_k 32, d_v 64 93.5 -> 80.8 with inputs in the
+// last-level cache, 20 % less from HBM; the rest beside the
 // rule, segment_chunks in gla_fwd.hip.
 // ---------------------------------------------------------------------------
 template <class L>
